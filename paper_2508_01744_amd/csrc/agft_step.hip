@@ -227,14 +227,6 @@ static_assert(row_walk_consistent<8, 3, 8>() && row_walk_consistent<8, 4, 8>() &
                   row_walk_consistent<32, 3, 8>() && row_walk_consistent<32, 4, 8>(),
               "the update's row walk matches the record layout");
 
-// Column j and row i of packed element e.
-__device__ inline void unpack(int e, int &i, int &j) {
-    int c = 0;
-    while ((c + 1) * (c + 2) / 2 <= e) ++c;
-    j = c;
-    i = e - c * (c + 1) / 2;
-}
-
 // Per-instance block of 32-bit words: previous action, active-arm count,
 // non-finite-input count, mode (-1 exploring, else the round exploitation
 // began), the Page-Hinkley state (n, mean, m+, min m+, m-, min m-), the round
@@ -1396,64 +1388,84 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
 // ---- initialisation and export ----
 
 struct InitArgs {
-    float4 *arms;
-    uint32_t *mask;
-    int32_t *inst;
-    int2 *stats;
-    float4 *theta;        // [B][K][d/4] or nullptr
-    StateHeader *hdr;
+    char *base;           // the state buffer
+    Layout lay;
     StateHeader h;
-    int32_t B, K, KW, d, C, IW;
-    int32_t tf;           // tail floats per lane slice
+    int32_t B, K;
     int32_t stride0;      // stride of the starting action space
     float inv_sqrt_lambda;
 };
 
-__global__ void agft_init_kernel(InitArgs p) {
-    const size_t gtid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t gsz = (size_t)gridDim.x * blockDim.x;
-    // every chunk of every block, the arms past K of the last block zeroed
-    const int nb = 64 / p.d, main = (p.d / 2) * (p.d / 4), tail = (p.d / 2) * p.tf / 4;
-    const int blk = nb * p.C;
-    const size_t ic = (size_t)((p.K + nb - 1) / nb) * blk;
-    for (size_t idx = gtid; idx < (size_t)p.B * ic; idx += gsz) {
-        const int o = (int)(idx % ic % blk);
-        const int k = (int)(idx % ic / blk) * nb + (o < nb * main ? o / main : (o - nb * main) / tail);
-        const int c = o < nb * main ? o % main : main + (o - nb * main) % tail;
-        float v[4];
-        for (int q = 0; q < 4; ++q) {
-            const int ci = k < p.K ? canon_chunk(p.d, p.tf, c, q) : -1;
-            v[q] = 0.0f;
-            if (ci >= p.d) {
-                int i, col;
-                unpack(ci - p.d, i, col);
-                if (i == col) v[q] = p.inv_sqrt_lambda;
-            }
-        }
-        p.arms[idx] = make_float4(v[0], v[1], v[2], v[3]);
+// Record chunks per workgroup of the initialisation.
+constexpr int kInitThreads = 256, kInitChunks = kInitThreads;
+
+// Writes every byte of the state buffer (the gaps between regions as zeros).
+// Bound by HBM's write rate, so the values have to cost next to nothing: the
+// only elements of a record that are not zero are S_ii = 1/sqrt(lambda), at
+// positions j and j+1 of lane slice j (columns j and D-1-j), all in the main
+// part, and a chunk's place in its block comes from divisions by constants.
+// One chunk per thread, each workgroup's contiguous.  Measured on MI355X with
+// 65,536 x 128 x 16 (5.17 GB): 5,080 us with the index of every element
+// unpacked by a loop behind 64-bit divisions; so, 845 us (6.1 TB/s), 906 us
+// with two chunks per thread, 915 us with eight.  1,024 x 256 x 32: 1,040 ->
+// 99 us.
+template <int D, int TF>
+__global__ __launch_bounds__(kInitThreads) void agft_init_kernel(InitArgs p) {
+    using R = Rec<D, TF>;
+    constexpr int IW = (kInstX + D + 15) / 16 * 16;   // inst_words(D)
+    const int tid = threadIdx.x;
+    const uint32_t KB = (uint32_t)(p.K + R::NB - 1) / R::NB;
+    const uint64_t chunks = (uint64_t)p.B * KB * R::BLK;
+    const int tail_arms = p.K % R::NB;   // arms of an instance's last block, if part-filled
+    const uint64_t c0 = (uint64_t)blockIdx.x * kInitChunks;
+    const uint64_t blk0 = c0 / R::BLK;
+    const uint32_t o0 = (uint32_t)(c0 - blk0 * R::BLK);
+    const uint32_t kb0 = (uint32_t)(blk0 % KB);
+    float4 *arms = reinterpret_cast<float4 *>(p.base + p.lay.arms) + c0;
+    const uint32_t left = chunks - c0 < (uint64_t)kInitChunks ? (uint32_t)(chunks - c0) : (uint32_t)kInitChunks;
+#pragma unroll
+    for (int q = 0; q < kInitChunks / kInitThreads; ++q) {
+        const uint32_t c = (uint32_t)(q * kInitThreads + tid);
+        const uint32_t b = (o0 + c) / R::BLK, o = (o0 + c) % R::BLK;
+        const int cc = (int)(o % R::MAIN), j = cc % R::G, e0 = 4 * (cc / R::G);
+        bool arm = o < (uint32_t)(R::NB * R::MAIN);
+        if (tail_arms != 0) arm = arm && ((int)(o / R::MAIN) < tail_arms || (kb0 + b) % KB != KB - 1);
+        nt_f4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = arm && (e0 + e == j || e0 + e == j + 1) ? p.inv_sqrt_lambda : 0.0f;
+        if (c < left) *reinterpret_cast<nt_f4 *>(arms + c) = v;
     }
-    const size_t nmask = (size_t)p.B * p.KW;
-    for (size_t idx = gtid; idx < nmask; idx += gsz) {
-        const int w = (int)(idx % p.KW);
-        const int rem = p.K - 32 * w;
-        p.mask[idx] = rem >= 32 ? 0xffffffffu : ((1u << rem) - 1u);
-    }
-    for (size_t idx = gtid; idx < (size_t)p.B * p.K; idx += gsz) p.stats[idx] = make_int2(0, 0);
-    if (p.theta != nullptr)
-        for (size_t idx = gtid; idx < (size_t)p.B * p.K * (p.d / 4); idx += gsz)
-            p.theta[idx] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (size_t idx = gtid; idx < (size_t)p.B * p.IW; idx += gsz) {
-        const int w = (int)(idx % p.IW);
+
+    const uint64_t gtid = (uint64_t)blockIdx.x * kInitThreads + tid;
+    const uint64_t gsz = (uint64_t)gridDim.x * kInitThreads;
+    // masks, every arm in play, and the gaps before and after them
+    const uint32_t KW = (uint32_t)(p.K + 31) / 32;
+    const uint32_t last = p.K % 32 ? (1u << (p.K % 32)) - 1u : 0xffffffffu;
+    uint32_t *mask = reinterpret_cast<uint32_t *>(p.base + p.lay.mask);
+    const uint64_t nmask = (uint64_t)p.B * KW;
+    for (uint64_t idx = gtid; idx < (p.lay.inst - p.lay.mask) / 4; idx += gsz)
+        mask[idx] = idx >= nmask ? 0u : last == 0xffffffffu || idx % KW != KW - 1 ? 0xffffffffu : last;
+    uint32_t *pad = reinterpret_cast<uint32_t *>(p.base + p.lay.arms) + chunks * 4;
+    for (uint64_t idx = gtid; idx < (p.lay.mask - p.lay.arms) / 4 - chunks * 4; idx += gsz) pad[idx] = 0u;
+    // instance blocks
+    int32_t *inst = reinterpret_cast<int32_t *>(p.base + p.lay.inst);
+    const uint64_t ninst = (uint64_t)p.B * IW;
+    for (uint64_t idx = gtid; idx < (p.lay.stats - p.lay.inst) / 4; idx += gsz) {
+        const int w = (int)(idx % IW);
         const int hi = p.K - 1;
-        const int kact0 = (hi - 0) / p.stride0 + 1;   // arms on the starting grid
-        p.inst[idx] = w == kInstAprev || w == kInstMode ? -1
-                    : w == kInstKact ? kact0
-                    : w == kInstPhMargin ? 0x7f800000   // +inf: no test yet
-                    : w == kInstHi ? hi
-                    : w == kInstStride ? p.stride0
-                    : 0;
+        inst[idx] = idx >= ninst ? 0
+                  : w == kInstAprev || w == kInstMode ? -1
+                  : w == kInstKact ? hi / p.stride0 + 1   // arms on the starting grid
+                  : w == kInstPhMargin ? 0x7f800000       // +inf: no test yet
+                  : w == kInstHi ? hi
+                  : w == kInstStride ? p.stride0
+                  : 0;
     }
-    if (gtid == 0) *p.hdr = p.h;
+    // reward counts and sums, the theta copy: zeros to the end of the buffer
+    float4 *zero = reinterpret_cast<float4 *>(p.base + p.lay.stats);
+    for (uint64_t idx = gtid; idx < (p.lay.total - p.lay.stats) / 16; idx += gsz)
+        zero[idx] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (gtid == 0) *reinterpret_cast<StateHeader *>(p.base) = p.h;
 }
 
 template <int D, int TF>
@@ -1563,6 +1575,19 @@ template <class T>
 T *at(char *base, size_t off) {
     return reinterpret_cast<T *>(base + off);
 }
+
+// fn(d, tail floats) with both as compile-time constants, for a supported d.
+template <class Fn>
+void for_layout(int d, int tf, Fn fn) {
+    auto with_d = [&](auto dc) {
+        if (tf == 3) fn(dc, std::integral_constant<int, 3>{});
+        else fn(dc, std::integral_constant<int, 4>{});
+    };
+    if (d == 8) with_d(std::integral_constant<int, 8>{});
+    else if (d == 16) with_d(std::integral_constant<int, 16>{});
+    else with_d(std::integral_constant<int, 32>{});
+}
+
 // agft_sim_step runs the environment in the step kernel's epilogue up to
 // this many instances, and launches the step and environment kernels above.
 constexpr int kFusedMaxB = 8192;
@@ -1778,27 +1803,18 @@ int agft_create(const agft_config *cfg, void *d_state, size_t nbytes, void *stre
         return AGFT_OK;
     }
     InitArgs a;
-    a.arms = at<float4>(h->base, lay.arms);
-    a.mask = at<uint32_t>(h->base, lay.mask);
-    a.inst = at<int32_t>(h->base, lay.inst);
-    a.stats = at<int2>(h->base, lay.stats);
-    a.theta = cfg->exploit ? at<float4>(h->base, lay.theta) : nullptr;
-    a.hdr = at<StateHeader>(h->base, 0);
+    a.base = h->base;
+    a.lay = lay;
     a.h = want;
     a.B = cfg->B;
     a.K = cfg->K;
-    a.KW = (cfg->K + 31) / 32;
-    a.d = cfg->d;
-    a.tf = tail_floats(*cfg);
-    a.C = chunks_for(cfg->d, a.tf);
-    a.IW = inst_words(cfg->d);
     a.stride0 = cfg->refine ? cfg->refine_stride : 1;
     a.inv_sqrt_lambda = (float)(1.0 / std::sqrt((double)cfg->lambda));
-    const size_t work = (size_t)cfg->B * a.C * cfg->K;
-    size_t blocks = (work + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(agft_init_kernel, dim3((unsigned)blocks), dim3(256), 0, h->stream, a);
+    const size_t chunks = (size_t)cfg->B * instance_chunks(cfg->K, cfg->d, want.tail_floats);
+    const dim3 grid((unsigned)((chunks + kInitChunks - 1) / kInitChunks)), block(kInitThreads);
+    for_layout(cfg->d, want.tail_floats, [&](auto d, auto tf) {
+        hipLaunchKernelGGL((agft_init_kernel<d.value, tf.value>), grid, block, 0, h->stream, a);
+    });
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         delete h;

@@ -67,8 +67,8 @@ class Tuner:
         if state is None:
             if adopt:
                 raise ValueError("adopt=True needs an existing state buffer")
-            # zeroed so that the alignment gaps between regions are deterministic
-            state = torch.zeros(self.nbytes, dtype=torch.uint8, device=self.device)
+            # (agft_create writes every byte of it)
+            state = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
         if state.dtype != torch.uint8 or state.dim() != 1 or not state.is_contiguous():
             raise ValueError("state must be a contiguous 1-D uint8 tensor")
         if state.data_ptr() % 256 != 0:
