@@ -53,3 +53,49 @@ def test_fresh_state_is_written_whole(B, K, d, opts):
     nonzero = np.count_nonzero(state.cpu().numpy()[256:])
     regions = sum(np.count_nonzero(np.ascontiguousarray(v[k].cpu().numpy()).view(np.uint8)) for k in ("arms", "mask", "inst"))
     assert nonzero == regions
+
+
+def _random_models(t, seed):
+    """Random records in t's buffer; returns theta and S as the layout decodes them."""
+    v = t.view()
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    keep = v["arms"] != 0                                        # the diagonal
+    tf = (v["arms"].shape[2] // (64 // t.d) - (t.d // 2) * (t.d // 4)) * 4 // (t.d // 2)
+    theta1, S1 = _decode(torch.ones_like(v["arms"]).cpu().numpy(), t.K, t.d, tf)
+    v["arms"].normal_(generator=g)
+    v["arms"].add_(keep * 1.5)
+    theta, S = _decode(v["arms"].cpu().numpy(), t.K, t.d, tf)
+    assert theta1.all() and np.count_nonzero(S1) == S1.size // t.d * (t.d + 1) // 2
+    return theta, S
+
+
+@pytest.mark.parametrize("prune", [0, 1])
+@pytest.mark.parametrize("B,K,d", SIZES + [(4, 40, 16), (17, 8, 32), (1, 64, 8)])
+def test_export_is_the_records_product(B, K, d, prune):
+    """theta as stored; each entry of S S^T within the bound of a sum of up to
+    d fused products in single precision.  Outputs at any float's address."""
+    t = Tuner(B, K, d, prune_rule=prune)
+    theta, S = _random_models(t, 17 * B + K)
+    th, ai = t.export(theta=True, ainv=True)
+    say(f"[export] B={B} K={K} d={d}")
+    assert np.array_equal(theta, th.cpu().numpy())
+    S = S.astype(np.float64)
+    ref, mag = S @ S.swapaxes(2, 3), np.abs(S) @ np.abs(S).swapaxes(2, 3)
+    assert (np.abs(ai.cpu().numpy() - ref) <= (d + 1) * 2.0 ** -24 * mag).all()
+    from paper_2508_01744_amd import _lib as L
+    th1, ai1 = (torch.full((x.numel() + 2,), 7.0, device="cuda") for x in (th, ai))
+    L.check("agft_export", L.agft_export(t.h, th1.data_ptr() + 4, ai1.data_ptr() + 4))
+    for whole, want in ((th1, th), (ai1, ai)):
+        assert torch.equal(whole[1:-1], want.reshape(-1)) and whole[0] == 7.0 and whole[-1] == 7.0
+
+
+def test_export_keeps_infinities_to_their_entries():
+    """An infinite factor element reaches the products that hold it and no other."""
+    B, K, d = 3, 9, 16
+    t = Tuner(B, K, d)
+    _random_models(t, 5)
+    v = t.view()
+    v["arms"][1, 1, 0, 0] = float("inf")     # S_00 of arm 4: A^-1_00 alone
+    _, ai = t.export(theta=False, ainv=True)
+    bad = ~torch.isfinite(ai)
+    assert bad.nonzero().tolist() == [[1, 4, 0, 0]]
