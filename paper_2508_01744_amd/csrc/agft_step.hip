@@ -130,15 +130,6 @@ __host__ __device__ constexpr int canon(int D, int j, int e) {
          : -1;
 }
 
-// Chunk c of arm k's record, as an offset (in chunks) from the instance's
-// first block: chunks 0..MAIN-1 are the main part, the rest the tail.
-__host__ __device__ constexpr size_t rec_chunk(int D, int TF, int k, int c) {
-    const int G = D / 2, NB = 64 / D, MAIN = G * (D / 4), TAIL = G * TF / 4;
-    const size_t blk = (size_t)(k / NB) * NB * (MAIN + TAIL);
-    return c < MAIN ? blk + (size_t)(k % NB) * MAIN + c
-                    : blk + (size_t)NB * MAIN + (size_t)(k % NB) * TAIL + (c - MAIN);
-}
-
 // Canonical index of component q of record chunk c; -1 for padding.
 __host__ __device__ constexpr int canon_chunk(int D, int TF, int c, int q) {
     const int G = D / 2, MAIN = G * (D / 4);
@@ -344,19 +335,34 @@ int waves_at(const agft_config &c, int64_t t) {
 // 220.8 us; K=256 d=32 B=1,024 92.4 / 91.7 us.
 bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <= 16384; }
 
-// Per-lane slice of the Eq. 1 terms from the S chunks of one record slice:
-// va, vb = the two owned entries of S^T x, m = the two owned theta terms.
-// xa/xb hold x_e (e <= j) and x_{D-e} (e > j) for this lane's positions.
+// What lane j of a group multiplies the positions of its record slice with.
+// Positions e <= j belong to column j (times x_e), positions e > j to column
+// D-1-j (times x_{D-e}).  With j < G = D/2, position 0 is always of the first
+// kind and positions G..D always of the second: those take elements of x that
+// are the same in every lane, from scalar registers (u), and only positions
+// 1..G-1 need a selected pair (a, b; one of the two is 0).
 template <int D>
-__device__ __forceinline__ void slice_terms(const float *f, const float *xa, const float *xb,
-                                            float xt0, float xt1, float &m, float &w2) {
-    float va = 0.0f, vb = 0.0f;
+struct SliceX {
+    static constexpr int G = D / 2;
+    float u[G + 1];      // x_0..x_G
+    float a[G], b[G];    // [e], 1 <= e < G: e <= j ? x_e : 0 and e > j ? x_{D-e} : 0
+    float t0, t1;        // x_{2j}, x_{2j+1}
+};
+
+// Per-lane slice of the Eq. 1 terms from the positions f of one record slice:
+// m, the two owned terms of theta^T x, and w2, the squares of the two owned
+// entries of S^T x.
+template <int D>
+__device__ __forceinline__ void slice_terms(const float *f, const SliceX<D> &x, float &m, float &w2) {
+    constexpr int G = D / 2;
+    float va = f[0] * x.u[0], vb = f[1] * x.b[1];
 #pragma unroll
-    for (int e = 0; e <= D; ++e) {
-        va = fmaf(f[e], xa[e], va);
-        vb = fmaf(f[e], xb[e], vb);
-    }
-    m = fmaf(f[D + 2], xt1, f[D + 1] * xt0);
+    for (int e = 1; e < G; ++e) va = fmaf(f[e], x.a[e], va);
+#pragma unroll
+    for (int e = 2; e < G; ++e) vb = fmaf(f[e], x.b[e], vb);
+#pragma unroll
+    for (int e = G; e <= D; ++e) vb = fmaf(f[e], x.u[D - e], vb);
+    m = fmaf(f[D + 2], x.t1, f[D + 1] * x.t0);
     w2 = fmaf(vb, vb, va * va);
 }
 
@@ -459,10 +465,14 @@ __device__ __forceinline__ float4 ld_nt(const float4 *p) {
 // the same non-temporal hint only for d = 16.  Measured per step against
 // ordinary accesses: d = 16, -0.9% (65,536 x 128) and -0.4% (16,384 x 128);
 // d = 8, +5% (4,096 x 64); d = 32, +3% (1,024 x 256).
+// The gather goes from memory to LDS without registers: 16 bytes per lane,
+// lane l's to dst[l] (dst the same in every lane).  It has landed once vmcnt
+// says so.
 template <int D>
-__device__ __forceinline__ float4 ld_record(const float4 *p) {
-    if constexpr (D == 16) return ld_nt(p);
-    else return *p;
+__device__ __forceinline__ void load_to_lds(const float4 *src, float4 *dst) {
+    constexpr int kNonTemporal = 2;   // gfx9 cache policy bit
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, D == 16 ? kNonTemporal : 0);
 }
 template <int D>
 __device__ __forceinline__ void st_record(float4 *p, float x, float y, float z, float w) {
@@ -506,14 +516,37 @@ __device__ __forceinline__ int partner(int v) {
 template <int STEP>
 __device__ __forceinline__ float partner(float v) { return __int_as_float(partner<STEP>(__float_as_int(v))); }
 
+// The two values that lanes of neighbouring rows (SPAN 16) or half-waves
+// (SPAN 32) hold, in every lane of the pair: a swap on the vector unit,
+// without the LDS round trip of a permute.
+struct LanePair {
+    int lo, hi;
+};
+template <int SPAN>
+__device__ __forceinline__ LanePair lane_pair(int v) {
+    if constexpr (SPAN == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+        return LanePair{(int)r[0], (int)r[1]};
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+        return LanePair{(int)r[0], (int)r[1]};
+    }
+}
+template <int SPAN, class T, class Op>
+__device__ __forceinline__ T across(T v, Op op) {
+    static_assert(sizeof(T) == 4, "one register");
+    const LanePair r = lane_pair<SPAN>(__builtin_bit_cast(int, v));
+    return op(__builtin_bit_cast(T, r.lo), __builtin_bit_cast(T, r.hi));
+}
+
 template <class T, class Op>
 __device__ __forceinline__ T wave_reduce(T v, Op op) {
     v = op(v, partner<0>(v));
     v = op(v, partner<1>(v));
     v = op(v, partner<2>(v));
     v = op(v, partner<3>(v));
-    v = op(v, partner<4>(v));
-    return op(v, partner<5>(v));
+    v = across<16>(v, op);
+    return across<32>(v, op);
 }
 
 __device__ __forceinline__ BestPair wave_best(BestPair b) {
@@ -525,6 +558,28 @@ __device__ __forceinline__ BestPair wave_best(BestPair b) {
     step(BestPair{partner<4>(b.v), partner<4>(b.k)});
     step(BestPair{partner<5>(b.v), partner<5>(b.k)});
     return b;
+}
+
+// The arm of the wavefront's best pair: the largest value as an ordered
+// integer (negative floats with their magnitude bits flipped, -0 as +0), then
+// the smallest index that holds it.  Half the instructions of reducing pairs.
+// v is never a NaN (better() takes none).
+__device__ __forceinline__ int wave_best_arm(BestPair b) {
+    auto dpp_op = [](int v, auto ctrl, int identity, auto op) {
+        return op(v, __builtin_amdgcn_update_dpp(identity, v, decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    auto reduce = [&](int v, int identity, auto op) {
+        v = dpp_op(v, std::integral_constant<int, 0xB1>{}, identity, op);
+        v = dpp_op(v, std::integral_constant<int, 0x4E>{}, identity, op);
+        v = dpp_op(v, std::integral_constant<int, 0x141>{}, identity, op);
+        v = dpp_op(v, std::integral_constant<int, 0x140>{}, identity, op);
+        v = across<16>(v, op);
+        return across<32>(v, op);
+    };
+    const int bits = __float_as_int(b.v + 0.0f);
+    const int key = bits ^ ((bits >> 31) & 0x7fffffff);
+    const int top = reduce(key, (int)0x80000000, [](int x, int y) { return x > y ? x : y; });
+    return reduce(key == top ? b.k : 0x7fffffff, 0x7fffffff, [](int x, int y) { return x < y ? x : y; });
 }
 
 // Inclusive prefix sum within aligned segments of SEG lanes (8, 16 or 32):
@@ -555,10 +610,10 @@ __device__ __forceinline__ float segment_scan(float v, int lane) {
 // total of its column (lane % SEG) over the segments.
 template <int SEG>
 __device__ __forceinline__ float segment_colsum(float v) {
+    auto add = [](float a, float b) { return a + b; };
     if constexpr (SEG == 8) v += dpp<0x128>(v);   // row_ror:8, the other half row
-    if constexpr (SEG <= 16) v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    if constexpr (SEG <= 16) v = across<16>(v, add);
+    return across<32>(v, add);
 }
 
 // Workgroup-wide reductions through one LDS slot per wavefront (a
@@ -604,6 +659,21 @@ int occupancy_for(const agft_config &c, int tail) {
 // chains with little to stream.
 int cu_workgroups_for(int waves, int simd_waves) { return waves == 4 && simd_waves == 6 ? 4 : 0; }
 
+// What bounds the kernel: HBM's rate where a batch streams many bytes, else
+// one instance's chain of dependent phases and the instructions that it
+// issues, four cycles each whether vector or scalar (half to two thirds of
+// the time of the small batches).  Hence: the previous record goes straight to
+// LDS and the first pass is requested beside it, not after it; the list comes
+// from the mask words in scalar registers; what every lane multiplies by the
+// same element of x takes it from a scalar register; roots are taken once per
+// arm in the epilogue, 64 arms at a time, not once per pass by every lane; the
+// updated arm takes a slot of the stream's last pass; and one wavefront takes
+// the argmax while the others write the record back.  Measured on MI355X
+// against none of these (us per step): K=256 d=32 B=1,024 with three arms left
+// 9.25 -> 7.04, K=64 d=8 B=4,096 with the environment's kernel 16.44 -> 15.33,
+// K=129 d=16 B=1,000 with the score dump 15.22 -> 14.54; batches at HBM's rate
+// unchanged.
+//
 // ENV: the simulator's environment responds in the epilogue (agft_sim_step):
 // once the decision is known, the first lanes of wavefront 0 run the
 // instance's next window with it, writing the reward and the next context in
@@ -615,7 +685,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ENV && 
 void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     using R = Rec<D, TF>;
     constexpr int G = R::G, S = R::S;
-    constexpr int NQ = (R::R + kWave - 1) / kWave;   // update-record chunks per thread (>= 64 threads)
+    // The previous decision's record is fetched and written back by the
+    // wavefronts other than 0, which has the list and the argmax to do (one
+    // wavefront does it all): thread u0 and up, NQ chunks each.
+    constexpr int u0 = NW > 1 ? kWave : 0, NU = NW * kWave - u0;
+    constexpr int NQ = (R::R + NU - 1) / NU;
     const int inst = blockIdx.x;
     const int tid = threadIdx.x;
     constexpr int nthr = NW * kWave;   // the launch's workgroup width, fixed per instantiation
@@ -632,16 +706,17 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
 
     // the previous decision's record before and after its update, chunks in
     // record order (the layout of the arm's record in HBM)
-    __shared__ float4 s_old4[R::R];
+    __shared__ float4 s_old4[(R::R + kWave - 1) / kWave * kWave];   // (and slack for load_to_lds)
     __shared__ float4 s_new4[R::R];
     float *s_old = reinterpret_cast<float *>(s_old4);
     float *s_new = reinterpret_cast<float *>(s_new4);
     __shared__ float s_fpart[NW][D];   // per-wavefront partial sums of f = S^T xp
-    // per-arm scores and the list of arms to stream, sized by K at launch
-    // (step_lds_bytes) so that small arm counts leave room for more workgroups
+    // per arm, (theta^T x, |S^T x|^2) as the stream leaves them, then (UCB, LCB)
+    // where a later phase reads them by arm; and the list of arms to score.
+    // Sized by K at launch (step_lds_bytes) so that small arm counts leave room
+    // for more workgroups.
     extern __shared__ float s_arm[];
-    float *s_ucb = s_arm;
-    float *s_lcb = s_arm + K;
+    float2 *s_sc = reinterpret_cast<float2 *>(s_arm);
     short *s_list = reinterpret_cast<short *>(s_arm + 2 * K);
     __shared__ uint32_t s_mask[kMaxWords];
     __shared__ int s_nlist;
@@ -654,7 +729,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     __shared__ int s_red_k2[kMaxWaves];
 
     __shared__ float s_xp[D];   // context of the previous decision, for the update
-    __shared__ int2 s_stu;      // its arm's reward count and sum
+    __shared__ int s_stu[kWave];   // its arm's reward count and sum (fp32 bits), then slack
 
     const bool decide = p.ctx != nullptr;
     int32_t *blk = p.inst + (size_t)inst * p.IW;
@@ -662,11 +737,10 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // requested at once, so that the prologue waits for one memory round trip
     // rather than one per item (the vector loads first: the compiler's waits
     // for the addresses of later ones would hold them back behind the scalar
-    // loads).  Vector loads, by wavefront 0: the environment's state of the
-    // instance (for the epilogue), the instance's mask words and the previous
-    // decision's context; at D = 32 also the context, by every wavefront.
-    // Scalar loads: the instance's first sixteen words, the reward and, up
-    // to D = 16, the context.
+    // loads).  Vector loads: the context, by every wavefront; by wavefront 0
+    // the environment's state of the instance (for the epilogue), the
+    // instance's mask words and the previous decision's context.  Scalar
+    // loads: the instance's first sixteen words and the reward.
     __shared__ uint32_t s_envw[ENV ? 32 : 1];
     uint32_t env_pre = 0u;
     if constexpr (ENV)
@@ -685,52 +759,46 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // (no branch around the reward either: without a pending decision the
     // block's first word stands in for it, unused)
     const float r_in = *(p.apply_update ? p.reward + inst : reinterpret_cast<const float *>(blk));
-    // The context, without a branch: a flush reads the block's own words in
-    // its place, and nothing uses them (x_ok is false, so no arm is listed,
-    // scored or stashed).  Non-finite test on the exponent bits (both
-    // operands of the and evaluated: a short-circuit branch would hold back
-    // the loads after it).  Up to D = 16 the context comes by scalar loads;
-    // at D = 32 lane l < D reads element l and the selectors below take the
-    // values from the lanes, so that 32 scalar registers are not held while
-    // the loads are in flight (they would push the scalar loads apart).
-    const float *xi = decide ? p.ctx + (size_t)inst * D : reinterpret_cast<const float *>(blk);
-    float x[D];
-    float x_lane;   // element `lane` of the context, lanes < D
-    bool x_ok;
-    if constexpr (D <= 16) {
-        uint32_t nonfinite = 0u;
-#pragma unroll
-        for (int q = 0; q < D; ++q) {
-            x[q] = xi[q];
-            nonfinite |= (__float_as_uint(x[q]) & 0x7f800000u) == 0x7f800000u ? 1u : 0u;
-        }
-        x_ok = decide & (nonfinite == 0u);
-        x_lane = pick<D>(x, lane);
-    } else {
-        x_lane = xi[lane_d];
-        x_ok = decide & (__ballot((__float_as_uint(x_lane) & 0x7f800000u) == 0x7f800000u) == 0ull);
-#pragma unroll
-        for (int q = 0; q < D; ++q) x[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x_lane), q));
-    }
+    // The context, element `lane` in lanes < D, without a branch: a flush reads
+    // the block's own words in its place, and nothing uses them (x_ok is false,
+    // so no arm is listed, scored or stashed).  Non-finite test on the exponent
+    // bits.
+    const float x_lane = (decide ? p.ctx + (size_t)inst * D : reinterpret_cast<const float *>(blk))[lane_d];
+    const bool x_ok = decide & (__ballot((__float_as_uint(x_lane) & 0x7f800000u) == 0x7f800000u) == 0ull);
 
-    // The context also waits in LDS for its later readers (the exploiting
-    // stream and the stash in the epilogue).
-    __shared__ float s_x[D];
-    if (wave == 0 && lane < D) s_x[lane] = x_lane;
-    // This lane's selectors of x: xa_e = x_e for e <= j, xb_e = x_{D-e} for e > j.
-    float xa[D + 1], xb[D + 1];
-#pragma unroll
-    for (int e = 0; e <= D; ++e) {
-        xa[e] = e <= j ? x[e] : 0.0f;
-        xb[e] = (e > j && e >= 1) ? x[D - e < 0 ? 0 : D - e] : 0.0f;
-    }
-    const float xt0 = pick<D>(x, 2 * j), xt1 = pick<D>(x, 2 * j + 1);
+    __shared__ float4 s_x4[D / 4];   // the context, for its readers below
+    float *s_x = reinterpret_cast<float *>(s_x4);
     const int a_prev = p.apply_update ? wa.x : -1;   // word kInstAprev
     const bool has_prev = a_prev >= 0 && a_prev < K;
     // (taken back to a scalar register: the select leaves it in a vector one)
     const float r = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(has_prev ? r_in : 0.0f)));
     const bool upd = has_prev && isfinite(r);
     const int a_upd = upd ? a_prev : -1;
+
+    // Record of the previous decision's arm, requested as soon as its index is
+    // known, straight into LDS (no registers, no staging), with its reward count
+    // and sum, so that the end of the step only stores them.  No branch around
+    // the loads (lanes past the record repeat its last chunk into the slack of
+    // s_old4, a step without an update reads arm 0's), so that the waits for
+    // the loads before them do not wait for these too.
+    const int rec_blk = upd ? a_prev / R::NB : 0, rec_slot = upd ? a_prev % R::NB : 0;
+    const uint32_t rec_main = (uint32_t)(rec_blk * R::BLK + rec_slot * R::MAIN);
+    const uint32_t rec_tail = (uint32_t)(rec_blk * R::BLK + R::NB * R::MAIN + rec_slot * R::TAIL - R::MAIN);
+    auto rec_at = [&](int c) { return (uint32_t)c + (c < R::MAIN ? rec_main : rec_tail); };
+    const bool gathers = NW == 1 || (wave > 0 && (wave - 1) * kWave < R::R);
+    if (gathers) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int c = tid - u0 + q * NU;
+            load_to_lds<D>(recs + rec_at(c < R::R ? c : R::R - 1), s_old4 + (wave * kWave - u0) + q * NU);
+        }
+        if (p.keep_stats && wave == u0 / kWave) {
+            // (its two words: lanes past 1 repeat the second)
+            const int *st = reinterpret_cast<const int *>(p.stats + (size_t)inst * K + (upd ? a_upd : 0));
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(st + (lane < 1 ? 0 : 1)),
+                                             (__attribute__((address_space(3))) void *)s_stu, 4, 0, 0);
+        }
+    }
 
     // Page-Hinkley test on the instance's rewards and the switch to greedy
     // exploitation (uniform scalar code, single precision, fixed order).
@@ -784,25 +852,17 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     const int sp_lo = wd.x, sp_hi = wd.y;
     const int sp_st = wd.z > 1 ? wd.z : 1;
     const bool reset = p.prune_reset && !greedy && x_ok;
-    if (wave == 0 && lane < KW) {
-        s_raw[lane] = raw_word;
-        s_mask[lane] = (reset ? 0xffffffffu : raw_word) & space_bits(lane, sp_lo, sp_hi, sp_st);
-    }
-    if (upd && wave == 0 && lane < D) s_xp[lane] = xp_word;
-
-    // Record of the previous decision's arm, requested once its index is
-    // known (after the LDS stores above, which would otherwise wait for it
-    // too) and staged in LDS before the stream.  Its reward count and sum
-    // are fetched with it, so that the end of the step only stores them.
-    float4 old_chunk[NQ];
-    int2 st_upd = make_int2(0, 0);
-    if (upd) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int c = tid + q * nthr;
-            if (c < R::R) old_chunk[q] = ld_record<D>(recs + rec_chunk(D, TF, a_upd, c));
+    uint32_t word = 0u;   // wavefront 0, lane < KW: the arms in play of mask word `lane`
+    if (wave == 0) {
+        if (lane < KW) {
+            word = (reset ? 0xffffffffu : raw_word) & space_bits(lane, sp_lo, sp_hi, sp_st);
+            s_raw[lane] = raw_word;
+            s_mask[lane] = word;
         }
-        if (p.keep_stats && tid == 0) st_upd = p.stats[(size_t)inst * K + a_upd];
+        if (lane < D) {
+            s_x[lane] = x_lane;
+            s_xp[lane] = xp_word;
+        }
     }
 
     // The paper's pruning rules (Sec. 4.3) on the arms active at step start,
@@ -812,7 +872,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         const int2 *st = p.stats + (size_t)inst * K;
         const Heuristics &h = p.h;
         auto act0 = [&](int k) { return ((s_mask[k >> 5] >> (k & 31)) & 1u) != 0; };
-        // means to s_lcb, counts to s_ucb (as int bits); both are rewritten by the stream
+        // counts (as int bits) and means to s_sc, which the stream rewrites
         int q = 0;
         float qsum = 0.0f, qbest = -INFINITY;
         for (int k = tid; k < K; k += nthr) {
@@ -824,8 +884,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
                 rs += r;
             }
             const float mean = n > 0 ? rs / (float)n : 0.0f;
-            s_lcb[k] = mean;
-            s_ucb[k] = __int_as_float(n);
+            s_sc[k] = make_float2(__int_as_float(n), mean);
             if (act0(k) && n >= h.hist_min_n) {
                 ++q;
                 qsum += mean;
@@ -845,16 +904,16 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             const float mu = qsum / (float)q;
             float acc = 0.0f;
             for (int k = tid; k < K; k += nthr) {
-                const int n = __float_as_int(s_ucb[k]);
-                if (act0(k) && n >= h.hist_min_n) acc += (s_lcb[k] - mu) * (s_lcb[k] - mu);
+                const int n = __float_as_int(s_sc[k].x);
+                if (act0(k) && n >= h.hist_min_n) acc += (s_sc[k].y - mu) * (s_sc[k].y - mu);
             }
             acc = block_reduce(acc, s_red_v, lane, wave, nwave, fsum);
             sigma = sqrtf(acc / (float)q);
         }
         auto gone = [&](int k) {
             if (!act0(k)) return false;
-            const int n = __float_as_int(s_ucb[k]);
-            const float mean = s_lcb[k];
+            const int n = __float_as_int(s_sc[k].x);
+            const float mean = s_sc[k].y;
             if ((h.mask & 2) && p.t < h.ext_rounds && n >= h.ext_min_n && mean < h.ext_thr) return true;
             if (hist_on && n >= h.hist_min_n && h.hist_kappa * sigma - (qbest - mean) < 0.0f) return true;
             return false;
@@ -883,7 +942,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             for (int k = tid; k < K; k += nthr)
                 if (act0(k)) {
                     first = k < first ? k : first;
-                    if (__float_as_int(s_ucb[k]) > 0) bk = better(bk, BestPair{s_lcb[k], k});
+                    if (__float_as_int(s_sc[k].x) > 0) bk = better(bk, BestPair{s_sc[k].y, k});
                 }
             bk = wave_best(bk);
             first = wave_reduce(first, [](int a, int b) { return a < b ? a : b; });
@@ -912,59 +971,98 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
                 s_raw[lane] &= ~removed;
                 p.mask[(size_t)inst * KW + lane] = s_raw[lane];
             }
-            s_mask[lane] = w;
+            s_mask[lane] = word = w;
         }
         __syncthreads();
     }
 
-    // Active arms other than the one being updated, in index order: one arm
-    // per lane, 64 at a time, each placed by the count of active lanes below
-    // it in the wavefront's ballot.
+    // Active arms other than the one being updated, in index order: 64 arms at
+    // a time, the two mask words taken to scalar registers, each arm placed by
+    // the count of active lanes below it.  The updated arm, if in play, takes
+    // the slot after them: it is scored from LDS.
+    int nlist = 0, upd_in = 0;
     if (wave == 0) {
-        int placed = 0;
+        if (!x_ok) word = 0u;
+        if (lane == KW - 1 && (K & 31) != 0) word &= (1u << (K & 31)) - 1u;
+        if (upd) {
+            upd_in = (int)((uint32_t)__builtin_amdgcn_readlane((int)word, a_upd >> 5) >> (a_upd & 31) & 1u);
+            if (lane == a_upd >> 5) word &= ~(1u << (a_upd & 31));
+        }
         for (int k0 = 0; k0 < K; k0 += kWave) {
-            const int k = k0 + lane;
-            const bool on = x_ok && k < K && k != a_upd && ((s_mask[k >> 5] >> (k & 31)) & 1u) != 0u;
-            const unsigned long long bal = __ballot(on);
-            if (on) s_list[placed + __popcll(bal & ((1ull << lane) - 1ull))] = (short)k;
-            placed += __popcll(bal);
+            // (lanes past the last word hold zeros)
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)word, k0 >> 5);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)word, (k0 >> 5) + 1);
+            const unsigned long long bal = (unsigned long long)hi << 32 | lo;
+            if (__builtin_amdgcn_inverse_ballot_w64(bal))
+                s_list[nlist + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))] = (short)(k0 + lane);
+            nlist += __popcll(bal);
         }
-        if (lane == 0) s_nlist = placed;
+        if (upd_in && lane == 0) s_list[nlist] = (short)a_upd;
+        if (NW > 1 && lane == 0) s_nlist = nlist | upd_in << 16;
+    }
+    if constexpr (NW > 1) {
+        __syncthreads();
+        const int packed_n = __builtin_amdgcn_readfirstlane(s_nlist);
+        nlist = packed_n & 0xffff;
+        upd_in = packed_n >> 16;
+    } else {
+        __syncthreads();   // (one wavefront: orders its LDS accesses)
     }
 
-    // The previous decision's record, fetched at kernel start, goes to LDS now,
-    // so that it holds no registers through the stream.
-    if (upd) {
-        if (tid == 0) s_stu = st_upd;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int c = tid + q * nthr;
-            if (c < R::R) s_old4[c] = old_chunk[q];
-        }
-    }
-    __syncthreads();
+    // Where the update of an exploring instance runs (early_update on the host):
+    // below D = 32 always early; and where the whole list fits in the first
+    // pass, no later pass can wait behind the update.
+    const bool early = D < 32 || p.early_update || nlist <= apw;
+    // arms the stream scores: with the early update, the updated arm as well
+    const int total = nlist + (early ? upd_in : 0);
+    // whether any group of this wavefront has an arm
+    const bool streams = !greedy && wave * (kWave / G) < total;
 
-    const int nlist = s_nlist;
     // Stream buffers: two sets of S slots per lane, used in turn, so that one
     // pass is scored while the next one's loads are in flight: the lane's
-    // main chunks, then its three tail floats.  The first pass is issued now
-    // and lands while the update below runs.
+    // main chunks, then its three tail floats.  The first pass is issued now,
+    // beside the previous record, so that the two round trips are one.
     float4 buf_a[S], buf_b[S];
-    auto fetch = [&](int k, float4 *dst) {
-        const float4 *blk = recs + (size_t)(k / R::NB) * R::BLK;
-        const float4 *src = blk + (k % R::NB) * R::MAIN + j;
+    const char *rec_bytes = reinterpret_cast<const char *>(recs);
+    auto fetch = [&](int slot, float4 *dst) {
+        if (slot >= nlist) return;
+        const uint32_t k = (uint32_t)s_list[slot];
+        const uint32_t b = k / R::NB * (R::BLK * 16), r = k % R::NB;
+        const uint32_t main = b + r * (R::MAIN * 16) + (uint32_t)j * 16;
+        const uint32_t tail = b + r * (R::TAIL * 16) + (uint32_t)j * (TF * 4) + R::NB * R::MAIN * 16;
 #pragma unroll
-        for (int sidx = 0; sidx < R::MQ; ++sidx) dst[sidx] = ld_nt(src + sidx * G);
-        const float *tail = reinterpret_cast<const float *>(blk + R::NB * R::MAIN + (k % R::NB) * R::TAIL) + TF * j;
-        const nt_f3 t = __builtin_nontemporal_load(reinterpret_cast<const nt_f3 *>(tail));
+        for (int sidx = 0; sidx < R::MQ; ++sidx)
+            dst[sidx] = ld_nt(reinterpret_cast<const float4 *>(rec_bytes + main + sidx * G * 16));
+        const nt_f3 t = __builtin_nontemporal_load(reinterpret_cast<const nt_f3 *>(rec_bytes + tail));
         dst[R::MQ] = make_float4(t.x, t.y, t.z, 0.0f);
     };
-    auto list_at = [&](int slot) { return slot < nlist ? (int)s_list[slot] : -1; };
-    int k_a = -1;
-    if (!greedy) {
-        k_a = list_at(grp);
-        if (k_a >= 0) fetch(k_a, buf_a);
-    }
+    // What this lane multiplies its slice's positions with (slice_terms):
+    // uniform elements of x in scalar registers, selected ones from LDS; formed
+    // by the wavefronts that stream, just before they do.
+    SliceX<D> sx;
+    auto selectors = [&]() {
+        typedef const float __attribute__((address_space(4))) *scalar_ptr;
+        const scalar_ptr xs = (scalar_ptr)(uintptr_t)(p.ctx + (size_t)inst * D);
+#pragma unroll
+        for (int e = 0; e <= G; ++e) sx.u[e] = xs[e];
+#pragma unroll
+        for (int e = 1; e < G; ++e) {
+            sx.a[e] = e <= j ? s_x[e] : 0.0f;
+            sx.b[e] = e > j ? s_x[D - e] : 0.0f;
+        }
+        const float2 xt = reinterpret_cast<const float2 *>(s_x)[j];
+        sx.t0 = xt.x;
+        sx.t1 = xt.y;
+    };
+
+    // Every wavefront sees the previous decision's record in LDS.
+    auto record_ready = [&]() {
+        if (gathers) {
+            // the loads to LDS have landed (gfx9 encoding: vmcnt 0 only)
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+        }
+        __syncthreads();
+    };
 
     // ---- square-root rank-1 update of the previous decision's arm ----
     // Run while the stream's first pass is in flight, or after the stream
@@ -1012,8 +1110,9 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             const float al_last = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), D - 1));
             // prediction error r - xp^T theta
             float pred = lane < D ? s_xp[lane] * s_old[rec_pos_theta<D, TF>(lane)] : 0.0f;
-            pred = wave_reduce(pred, [](float a, float b) { return a + b; });
-            const float err = r - pred;
+            pred = group_sum<D < 16 ? D : 16>(pred);
+            if constexpr (D == 32) pred = across<16>(pred, [](float a, float b) { return a + b; });
+            const float err = r - __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pred)));
             // row i of S' = S M:  S'_ij = ca_j S_ij - cb_j g_ij with g_ij the
             // exclusive prefix sum of f_q S_iq along the row; its total is
             // (S f)_i, so the gain is that total / alpha_{d-1} (one reciprocal
@@ -1050,139 +1149,127 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // their full latency.
     auto write_back = [&]() {
         if (upd) {
-            float4 *dst = p.arms + (size_t)inst * inst_chunks;
+            if (gathers) {
+                float4 *dst = p.arms + (size_t)inst * inst_chunks;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int c = tid + q * nthr;
-                if (c < R::R) {
-                    const float4 v = s_new4[c];
-                    st_record<D>(dst + rec_chunk(D, TF, a_upd, c), v.x, v.y, v.z, v.w);
+                for (int q = 0; q < NQ; ++q) {
+                    int c = tid - u0 + q * NU;
+                    asm("" : "+v"(c));   // the chunk's place again, not kept in a register through the stream
+                    if (c < R::R) {
+                        const float4 v = s_new4[c];
+                        st_record<D>(dst + rec_at(c), v.x, v.y, v.z, v.w);
+                    }
                 }
             }
-            if (p.theta != nullptr && tid < D / 4) {
+            const int ut = tid - u0;
+            if (p.theta != nullptr && ut >= 0 && ut < D / 4) {
                 float4 *tdst = reinterpret_cast<float4 *>(p.theta + ((size_t)inst * K + a_upd) * D);
-                tdst[tid] = make_float4(s_new[rec_pos_theta<D, TF>(4 * tid)], s_new[rec_pos_theta<D, TF>(4 * tid + 1)],
-                                        s_new[rec_pos_theta<D, TF>(4 * tid + 2)], s_new[rec_pos_theta<D, TF>(4 * tid + 3)]);
+                tdst[ut] = make_float4(s_new[rec_pos_theta<D, TF>(4 * ut)], s_new[rec_pos_theta<D, TF>(4 * ut + 1)],
+                                       s_new[rec_pos_theta<D, TF>(4 * ut + 2)], s_new[rec_pos_theta<D, TF>(4 * ut + 3)]);
             }
-            if (p.keep_stats && tid == 0)
+            if (p.keep_stats && ut == 0)
                 p.stats[(size_t)inst * K + a_upd] =
-                    make_int2(s_stu.x + 1, __float_as_int(__int_as_float(s_stu.y) + r));
+                    make_int2(s_stu[0] + 1, __float_as_int(__int_as_float(s_stu[1]) + r));
         }
     };
-    // The updated arm, scored on x_t from LDS exactly as the stream scores a
-    // record from HBM (same slices, same operation order).  With the early
-    // update it runs right after it, while the stream's first pass is in
-    // flight, instead of after the stream on the step's critical path.
-    auto score_updated = [&]() {
-        if (upd && x_ok && wave == 0) {
-            float f[4 * S];
+    // A slice of the updated arm's record from LDS, as the stream holds one.
+    auto updated_slice = [&](float4 *c4) {
 #pragma unroll
-            for (int sidx = 0; sidx < R::MQ; ++sidx) {
-                const float4 c4 = s_new4[sidx * G + j];
-                f[4 * sidx] = c4.x;
-                f[4 * sidx + 1] = c4.y;
-                f[4 * sidx + 2] = c4.z;
-                f[4 * sidx + 3] = c4.w;
-            }
-            const float *tl = s_new + 4 * R::MAIN + TF * j;
-            f[4 * R::MQ] = tl[0];
-            f[4 * R::MQ + 1] = tl[1];
-            f[4 * R::MQ + 2] = tl[2];
-            f[4 * R::MQ + 3] = 0.0f;
-            float m, w2;
-            slice_terms<D>(f, xa, xb, xt0, xt1, m, w2);
-            m = group_sum<G>(m);
-            w2 = group_sum<G>(w2);
-            if (lane == 0) {
-                const float w = sqrtf(w2);
-                s_ucb[a_upd] = greedy ? m : fmaf(p.alpha, w, m);
-                s_lcb[a_upd] = greedy ? m : fmaf(-p.alpha, w, m);
-            }
-        }
+        for (int sidx = 0; sidx < R::MQ; ++sidx) c4[sidx] = s_new4[sidx * G + j];
+        const float *tl = s_new + 4 * R::MAIN + TF * j;
+        c4[R::MQ] = make_float4(tl[0], tl[1], tl[2], 0.0f);
     };
-    // An exploiting instance has no pass in flight.  Where the whole list fits
-    // in the first pass, no later pass can wait behind the update.
-    const bool early = (p.early_update || nlist <= apw) && !greedy;
-    if (early) {
-        update();
-        score_updated();
-    }
+    auto score_updated = [&]() {
+        float4 c4[S];
+        updated_slice(c4);
+        const float *f = reinterpret_cast<const float *>(c4);
+        float m, w2;
+        slice_terms<D>(f, sx, m, w2);
+        m = group_sum<G>(m);
+        w2 = group_sum<G>(w2);
+        if (lane == 0) s_sc[a_upd] = make_float2(m, w2);
+    };
+    // One pass: the arm of this lane's group in slot `slot`.  The updated arm,
+    // in slot nlist, is scored from LDS exactly as the others are from HBM.
+    auto score = [&](float4 *c4, int slot) {
+        if (early && upd_in && slot - grp + apw > nlist) {   // the pass that holds slot nlist
+            if (slot == nlist) updated_slice(c4);
+        }
+        const float *f = reinterpret_cast<const float *>(c4);
+        float m, w2;
+        slice_terms<D>(f, sx, m, w2);
+        m = group_sum<G>(m);
+        w2 = group_sum<G>(w2);
+        if (slot < total && j == 0) s_sc[s_list[slot]] = make_float2(m, w2);
+    };
 
-    // ---- scoring of every listed arm (Eq. 1), two passes in flight ----
     if (greedy) {
         // Eq. 2: only theta_k^T x_t, read from the contiguous theta copy by
-        // groups of D/4 lanes (one float4 each)
-        constexpr int GT = D / 4;
-        const int jt = tid % GT, gt = tid / GT, apt = nthr / GT;
-        const float x0 = s_x[4 * jt], x1 = s_x[4 * jt + 1];
-        const float x2 = s_x[4 * jt + 2], x3 = s_x[4 * jt + 3];
-        const float4 *th = reinterpret_cast<const float4 *>(p.theta + (size_t)inst * K * D);
-        // UT passes' loads are issued before any of them is used, so that an
-        // instance waits for about one load latency per UT passes (three at
-        // d = 16 with seven wavefronts per SIMD, where four would spill).
-        // The explicit wait first (gfx9 encoding: vmcnt 0 only) clears the
-        // loads of the prologue, all consumed by now, from the compiler's
-        // count: otherwise a register they targeted, reused in the loop,
-        // would make it wait for every load in flight in each pass.
-        constexpr int UT = D == 16 && W >= 7 ? 3 : 4;
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        for (int base = 0; base < nlist; base += UT * apt) {
-            int kc[UT];
-            float4 v[UT];
+        // groups of D/4 lanes, one float4 each.  UT passes' loads are issued
+        // before any of them is used, so that an instance waits for one load
+        // latency per UT passes, the first of them beside the previous record's.
+        constexpr int GT = D / 4, APT = nthr / GT, UT = D == 32 ? 4 : 8;
+        int t = tid;
+        asm("" : "+v"(t));   // (keeps what follows out of the other branch's registers)
+        const int jt = t % GT, gt = t / GT;
+        const char *th_bytes = reinterpret_cast<const char *>(p.theta) + (size_t)inst * K * D * 4;
+        float4 v[UT];
+        auto theta_fetch = [&](int base) {
 #pragma unroll
             for (int u = 0; u < UT; ++u) {
-                const int slot = base + u * apt + gt;
-                kc[u] = slot < nlist ? s_list[slot] : -1;
-                v[u] = kc[u] >= 0 ? ld_nt(th + (size_t)kc[u] * GT + jt) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-#pragma unroll
-            for (int u = 0; u < UT; ++u) {
-                float m = kc[u] >= 0 ? fmaf(v[u].w, x3, fmaf(v[u].z, x2, fmaf(v[u].y, x1, v[u].x * x0))) : 0.0f;
-                m = group_sum<GT>(m);
-                if (kc[u] >= 0 && jt == 0) {
-                    s_ucb[kc[u]] = m;
-                    s_lcb[kc[u]] = m;
-                }
-            }
-        }
-    } else {
-        auto score = [&](const float4 *c4, int k) {
-            float f[4 * S];
-#pragma unroll
-            for (int sidx = 0; sidx < S; ++sidx) {
-                f[4 * sidx + 0] = c4[sidx].x;
-                f[4 * sidx + 1] = c4[sidx].y;
-                f[4 * sidx + 2] = c4[sidx].z;
-                f[4 * sidx + 3] = c4[sidx].w;
-            }
-            float m, w2;
-            slice_terms<D>(f, xa, xb, xt0, xt1, m, w2);
-            if (k < 0) {
-                m = 0.0f;
-                w2 = 0.0f;
-            }
-            m = group_sum<G>(m);
-            w2 = group_sum<G>(w2);
-            if (k >= 0 && j == 0) {
-                const float w = sqrtf(w2);
-                s_ucb[k] = fmaf(p.alpha, w, m);
-                s_lcb[k] = fmaf(-p.alpha, w, m);
+                const int slot = base + u * APT + gt;
+                if (slot < nlist)
+                    v[u] = ld_nt(reinterpret_cast<const float4 *>(th_bytes + (uint32_t)s_list[slot] * (D * 4) + jt * 16));
             }
         };
-        for (int base = 0; base < nlist; base += 2 * apw) {
-            const int k_b = list_at(base + apw + grp);
-            if (k_b >= 0) fetch(k_b, buf_b);
-            score(buf_a, k_a);
-            if (base + apw >= nlist) break;
-            k_a = list_at(base + 2 * apw + grp);
-            if (k_a >= 0) fetch(k_a, buf_a);
-            score(buf_b, k_b);
-        }
-    }
-
-    if (!early) {
+        theta_fetch(0);
+        record_ready();
         update();
-        score_updated();
+        const float4 x4 = s_x4[jt];
+        for (int base = 0; base < nlist;) {
+#pragma unroll
+            for (int u = 0; u < UT; ++u) {
+                const int slot = base + u * APT + gt;
+                float m = fmaf(v[u].w, x4.w, fmaf(v[u].z, x4.z, fmaf(v[u].y, x4.y, v[u].x * x4.x)));
+                m = group_sum<GT>(m);
+                if (slot < nlist && jt == 0) s_sc[s_list[slot]] = make_float2(m, 0.0f);
+            }
+            base += UT * APT;
+            if (base < nlist) theta_fetch(base);
+        }
+        // the updated arm, by the theta terms of its record
+        if (upd_in && wave == 0) {
+            const int jg = t % G;
+            const float2 xt = reinterpret_cast<const float2 *>(s_x)[jg];
+            const float *tl = s_new + 4 * R::MAIN + TF * jg;
+            const float m = group_sum<G>(fmaf(tl[2], xt.y, tl[1] * xt.x));
+            if (lane == 0) s_sc[a_upd] = make_float2(m, 0.0f);
+        }
+    } else {
+        if (streams) fetch(grp, buf_a);
+        record_ready();
+        if (early) update();
+        // ---- scoring of every listed arm (Eq. 1), two passes in flight ----
+        if (streams) {
+            selectors();
+            for (int base = 0;;) {
+                if (base + apw < nlist) fetch(base + apw + grp, buf_b);
+                score(buf_a, base + grp);
+                base += apw;
+                if (base >= total) break;
+                if (base + apw < nlist) fetch(base + apw + grp, buf_a);
+                score(buf_b, base + grp);
+                base += apw;
+                if (base >= total) break;
+            }
+        }
+        if (!early) {
+            update();
+            if (upd_in && wave == 0) {   // scored on its own, after the stream
+                selectors();
+                score_updated();
+            }
+        }
     }
 
     if (!decide) {
@@ -1218,16 +1305,35 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         write_back();
         return;
     }
-    __syncthreads();
-
     // ---- pruning and argmax over the scores in LDS ----
+    const bool prune_now = p.prune_now && !greedy;
+    const bool stat_anchor = p.rf.now && p.rf.stat;
+    float *sc = p.scores != nullptr ? p.scores + (size_t)inst * 2 * K : nullptr;
+    // Where nothing asks for the bounds by arm (no rule-1 step, score dump or
+    // statistical anchor), wavefront 0 alone walks the list; the others write
+    // the updated record back meanwhile and are done.
+    const bool by_list = !prune_now && sc == nullptr && !stat_anchor;
+    const int nplay = nlist + upd_in;
+    auto bounds_of = [&](float2 v) {   // (UCB, LCB); once exploiting both are theta^T x
+        const float w = sqrtf(v.y);
+        return greedy ? make_float2(v.x, v.x) : make_float2(fmaf(p.alpha, w, v.x), fmaf(-p.alpha, w, v.x));
+    };
+    if (NW > 1 && by_list && wave > 0) write_back();
+    __syncthreads();
+    if (NW > 1 && by_list && wave > 0) return;
+    if (!by_list) {
+        for (int slot = tid; slot < nplay; slot += nthr) {
+            const int k = s_list[slot];
+            s_sc[k] = bounds_of(s_sc[k]);
+        }
+        __syncthreads();
+    }
     auto is_active = [&](int k) { return k < K && ((s_mask[k >> 5] >> (k & 31)) & 1u) != 0; };
     float lstar = -INFINITY;
-    const bool prune_now = p.prune_now && !greedy;
     if (prune_now) {
         float l = -INFINITY;
         for (int k = tid; k < K; k += nthr)
-            if (is_active(k)) l = fmaxf(l, s_lcb[k]);
+            if (is_active(k)) l = fmaxf(l, s_sc[k].y);
         l = wave_reduce(l, [](float a, float b) { return fmaxf(a, b); });
         if (lane == 0) s_red_v[wave] = l;
         __syncthreads();
@@ -1236,14 +1342,18 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     }
     BestPair b{-INFINITY, 0x7fffffff};
     BestPair sb{-INFINITY, 0x7fffffff};   // statistical refinement anchor
-    const bool stat_anchor = p.rf.now && p.rf.stat;
     int n = 0;
-    float *sc = p.scores != nullptr ? p.scores + (size_t)inst * 2 * K : nullptr;
     float top1 = -INFINITY, top2 = -INFINITY;   // two largest kept scores (with the dump only)
+    if (by_list)
+        for (int slot = lane; slot < nplay; slot += kWave) {
+            const int k = s_list[slot];
+            b = better(b, BestPair{bounds_of(s_sc[k]).x, k});
+        }
+    else
     for (int base = 0; base < K; base += nthr) {
         const int k = base + tid;
         const bool act = is_active(k);
-        const float u = act ? s_ucb[k] : -INFINITY;
+        const float u = act ? s_sc[k].x : -INFINITY;
         const bool keep = act && !(u < lstar);
         n += __popcll(__ballot(keep));   // uniform over the wavefront
         if (keep) {
@@ -1256,14 +1366,14 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
                 // best mean reward among the arms with enough rewards (this
                 // step's update already counted: the updated arm's count and
                 // sum are written back only at the end of the step)
-                const int2 v = k == a_upd ? make_int2(s_stu.x + 1, __float_as_int(__int_as_float(s_stu.y) + r))
+                const int2 v = k == a_upd ? make_int2(s_stu[0] + 1, __float_as_int(__int_as_float(s_stu[1]) + r))
                                           : p.stats[(size_t)inst * K + k];
                 if (v.x >= p.rf.min_n) sb = better(sb, BestPair{__int_as_float(v.y) / (float)v.x, k});
             }
         }
         if (sc != nullptr && k < K) {
             sc[k] = u;
-            sc[K + k] = act ? s_lcb[k] : -INFINITY;
+            sc[K + k] = act ? s_sc[k].y : -INFINITY;
         }
         if (prune_now) {
             // clear the arms rule 1 removed from the global words (non-sticky:
@@ -1286,7 +1396,10 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             }
         }
     }
-    b = wave_best(b);
+    int best_arm = 0x7fffffff;
+    if (NW == 1 || by_list) best_arm = wave_best_arm(b);
+    else b = wave_best(b);
+    if (by_list) n = nplay;
     if (stat_anchor) sb = wave_best(sb);
     __shared__ float s_top[kMaxWaves][2];
     if (sc != nullptr) {
@@ -1307,7 +1420,8 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         }
     }
     // a one-wavefront workgroup has its results in every lane already
-    if constexpr (NW > 1) {
+    const bool merge_waves = NW > 1 && !by_list;
+    if (merge_waves) {
         if (lane == 0) {
             s_red_v[wave] = b.v;
             s_red_k[wave] = b.k;
@@ -1320,17 +1434,17 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     if (wave == 0) {
         // every lane of wavefront 0 reduces the per-wave results, then the
         // lanes write the instance block (action, count, context) at once
-        BestPair best = b;
         int cnt = n;
-        if constexpr (NW > 1) {
-            best = BestPair{s_red_v[0], s_red_k[0]};
+        if (merge_waves) {
+            BestPair best{s_red_v[0], s_red_k[0]};
             cnt = s_red_n[0];
             for (int w = 1; w < nwave; ++w) {
                 best = better(best, BestPair{s_red_v[w], s_red_k[w]});
                 cnt += s_red_n[w];
             }
+            best_arm = best.k;
         }
-        const int a = best.k == 0x7fffffff ? -1 : best.k;
+        const int a = best_arm == 0x7fffffff ? -1 : best_arm;
         // refinement after the decision: a window of 2*half+1 arms around the
         // anchor, every arm at full resolution, from the next step on
         int anchor = -1;
@@ -1384,7 +1498,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         // environment's response overwrites them in place
         if constexpr (ENV) agft_env_detail::env_epilogue(env, inst, a, lane, env_pre, s_envw);
     }
-    write_back();
+    if (NW == 1 || !by_list) write_back();
 }
 
 // ---- initialisation and export ----
