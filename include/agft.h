@@ -239,7 +239,12 @@ int agft_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32_t
               float *d_scores);
 
 /* How agft_step launches the step kernel for cfg (host-only, no device
- * call): one workgroup per instance.  The five fields follow from the
+ * call): one workgroup per instance.  (At 8,192 instances or more, 16,384 at
+ * d = 32, whose models in play fill 256 MB, 512 MB at d = 8, a decision with a
+ * pending reward takes two launches: the update of every instance's arm, in
+ * the order of sums of `waves`, then the step without it, whose workgroups
+ * have one wavefront up to 32 KB streamed per instance, 96 KB with rules 2, 4
+ * or 8, and four beyond.  The results are the same bits.)  The five fields follow from the
  * configuration alone: the bytes an exploring instance streams per step
  * (arms in play times 4(d + d(d+1)/2)) choose the record layout, with the
  * switch the bytes an exploiting instance streams choose the workgroup
@@ -257,7 +262,8 @@ typedef struct agft_launch_shape {
     int32_t early_update; /* 1: the rank-1 update runs while the stream's first pass
                              is in flight; 0: after the stream */
     int32_t cu_workgroups;  /* workgroups per compute unit agft_step's launch admits
-                               (its LDS request caps them there); 0: no cap.
+                               (its LDS request caps them there, beyond 64 KB
+                               streamed per instance); 0: no cap.
                                agft_sim_step's single launch is uncapped. */
 } agft_launch_shape;
 

@@ -335,6 +335,47 @@ int waves_at(const agft_config &c, int64_t t) {
 // 220.8 us; K=256 d=32 B=1,024 92.4 / 91.7 us.
 bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <= 16384; }
 
+// Whether the update of the previous decisions' arms is a kernel of its own,
+// ahead of one that only reads the records.  A write-back between the reads of
+// a stream at HBM's rate costs far more than its bytes (65,536 of 608 bytes:
+// 97 us of a 810 us stream, against 24 us for all of them on their own; a
+// 16-byte-per-lane read-only stream of the same 5.1 GB takes 713 us), so large
+// batches that stream from HBM are better off with a second launch.  Not where
+// the launch costs more than the interference saves: few instances, or records
+// that the Infinity Cache (256 MB) holds.  Measured on MI355X (us per step, in
+// one kernel / two):
+//   K=128 d=16: B=2,048 28.0 / 29.9, 4,096 53.3 / 52.3, 8,192 103.0 / 98.1,
+//     16,384 200 / 187, 65,536 795 / 737; with the refinement (21 arms) B=8,192
+//     25.8 / 27.6, 16,384 47.3 / 46.5, 32,768 91.2 / 87.3, 65,536 179 / 170;
+//     mostly exploiting B=4,096 24.0 / 26.5, 8,192 45.8 / 44.9, 65,536 297 / 267;
+//     rules 2-8 B=4,096 60.6 / 60.6, 16,384 210 / 194
+//   K=64 d=8: B=16,384 (184 MB) 40.0 / 44.4, 32,768 (369 MB) 77.6 / 82.0,
+//     65,536 163 / 161; K=256 d=8: B=8,192 (369 MB) 65.6 / 68.2, 16,384 130 / 126
+//   d=32, whose update is the longest: K=256 B=2,048 183 / 186, 4,096 374 / 362,
+//     with a quarter of the arms in play B=2,615 69.1 / 77.3; K=128 B=5,231 252 /
+//     243 and 74.5 / 81.9; K=32 B=20,926 269 / 264 and 122 / 106
+bool split_update(const agft_config &c) {
+    const size_t stream = (size_t)c.B * explore_bytes(c);
+    return c.B >= (c.d == 32 ? 16384 : 8192) && stream >= (size_t)(c.d == 8 ? 512 : 256) << 20;
+}
+
+// Workgroup width of the score kernel after a separate update: one wavefront
+// up to 32 KB per instance (96 KB with rules 2-8, which remove most arms in
+// the end), four beyond.  Without the update, an instance's chain is short and
+// one wavefront carries longer streams, and far more instances when few arms
+// are left.  Measured on MI355X with 1.5 GB of records (us per step, one
+// wavefront / four, every arm in play, then a quarter of them): d=16 K=32 (19
+// KB) 268 / 271 and 106 / 201, K=48 (29 KB) 256 / 243 and 94 / 144, K=64 (39
+// KB) 250 / 239 and 88 / 114, K=128 235 / 229 and 80 / 88; d=8 K=128 (23 KB)
+// 290 / 298 and 118 / 139, K=192 (34 KB) 281 / 270 and 116 / 121; d=32 K=20
+// (45 KB) 295 / 283 and 105 / 146.  With rules 2-8, K=128 d=16 B=16,384:
+// 193.6 / 195.1, with four arms in play 23.9 / 41.4.
+int score_waves_at(const agft_config &c, int64_t t) {
+    const bool may_exploit = c.exploit && t >= c.ph_min_rounds;
+    const size_t bytes = may_exploit ? (size_t)arms_in_play(c) * 4 * c.d : explore_bytes(c);
+    return bytes <= (size_t)((c.prune_rule & 14) ? 96 : 32) * 1024 ? 1 : 4;
+}
+
 // What lane j of a group multiplies the positions of its record slice with.
 // Positions e <= j belong to column j (times x_e), positions e > j to column
 // D-1-j (times x_{D-e}).  With j < G = D/2, position 0 is always of the first
@@ -582,20 +623,21 @@ __device__ __forceinline__ int wave_best_arm(BestPair b) {
     return reduce(key == top ? b.k : 0x7fffffff, 0x7fffffff, [](int x, int y) { return x < y ? x : y; });
 }
 
-// Inclusive prefix sum within aligned segments of SEG lanes (8, 16 or 32):
-// DPP shifts within rows of 16 lanes (zero-filled at row edges), masked at
-// the edges of 8-lane segments; for 32 lanes, the first row's total is then
-// added to the second row of each half-wavefront.
+// Inclusive prefix sum of a*b (prod, rounded) within aligned segments of SEG
+// lanes (8, 16 or 32): DPP shifts within rows of 16 lanes (zero-filled at row
+// edges), masked at the edges of 8-lane segments; for 32 lanes, the first
+// row's total is then added to the second row of each half-wavefront.  The
+// first addition takes a*b unrounded.
 template <int SEG>
-__device__ __forceinline__ float segment_scan(float v, int lane) {
+__device__ __forceinline__ float segment_scan(float a, float b, float prod, int lane) {
     static_assert(SEG == 8 || SEG == 16 || SEG == 32, "segments of 8, 16 or 32 lanes");
     auto shr = [](float x, auto ctrl) {
         return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value,
                                                           0xF, 0xF, true));
     };
     const int pos = lane & 7;
-    float s = shr(v, std::integral_constant<int, 0x111>{});    // row_shr:1
-    v += (SEG > 8 || pos >= 1) ? s : 0.0f;
+    float s = shr(prod, std::integral_constant<int, 0x111>{});    // row_shr:1
+    float v = fmaf(a, b, (SEG > 8 || pos >= 1) ? s : 0.0f);
     s = shr(v, std::integral_constant<int, 0x112>{});          // row_shr:2
     v += (SEG > 8 || pos >= 2) ? s : 0.0f;
     s = shr(v, std::integral_constant<int, 0x114>{});          // row_shr:4
@@ -657,7 +699,13 @@ int occupancy_for(const agft_config &c, int tail) {
 // instances in flight (K=128 d=16 B=65,536: 827.7 uncapped, 852.6 at 5,
 // 911.1 at 4), nor for one-wavefront workgroups, whose steps are short
 // chains with little to stream.
-int cu_workgroups_for(int waves, int simd_waves) { return waves == 4 && simd_waves == 6 ? 4 : 0; }
+// Nor up to 64 KB per instance, where the chain weighs more: the score kernel
+// at 4 / uncapped with 1.5 GB of records, d=16 K=32 324 / 271, K=48 258 / 244,
+// K=64 236 / 239, K=96 229 / 231, K=128 (76 KB) 229 / 233, and with a quarter
+// of the arms in play 269 / 201, 189 / 144, 147 / 114, 110 / 91, 88 / 82.
+int cu_workgroups_for(const agft_config &c, int waves, int simd_waves) {
+    return waves == 4 && simd_waves == 6 && explore_bytes(c) > 65536 ? 4 : 0;
+}
 
 // What bounds the kernel: HBM's rate where a batch streams many bytes, else
 // one instance's chain of dependent phases and the instructions that it
@@ -680,9 +728,11 @@ int cu_workgroups_for(int waves, int simd_waves) { return waves == 4 && simd_wav
 // place of the ones read.  The word each of those lanes prefetches costs a
 // register: at d = 16 the seven-wavefront form gets six, to fit without
 // spilling.
-template <int D, int TF, int W, int NW, bool ENV>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ENV && D == 16 && W > 6 ? W - 1 : W)))
-void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
+//
+// FOLD: the previous decision's reward is folded in by this kernel (else
+// agft_update_kernel has done it).
+template <int D, int TF, int NW, bool ENV, bool FOLD, int NBUF = 2>
+__device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_detail::EnvArgs &env) {
     using R = Rec<D, TF>;
     constexpr int G = R::G, S = R::S;
     // The previous decision's record is fetched and written back by the
@@ -752,7 +802,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     float xp_word = 0.0f;
     if (wave == 0) {
         raw_word = *mask_at;
-        xp_word = *xp_at;
+        if constexpr (FOLD) xp_word = *xp_at;
     }
     const int4 *blk4 = reinterpret_cast<const int4 *>(blk);
     const int4 wa = blk4[0], wb = blk4[1], wc = blk4[2], wd = blk4[3];
@@ -773,7 +823,8 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // (taken back to a scalar register: the select leaves it in a vector one)
     const float r = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(has_prev ? r_in : 0.0f)));
     const bool upd = has_prev && isfinite(r);
-    const int a_upd = upd ? a_prev : -1;
+    const bool fold = FOLD && upd;
+    const int a_upd = fold ? a_prev : -1;
 
     // Record of the previous decision's arm, requested as soon as its index is
     // known, straight into LDS (no registers, no staging), with its reward count
@@ -781,11 +832,11 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // the loads (lanes past the record repeat its last chunk into the slack of
     // s_old4, a step without an update reads arm 0's), so that the waits for
     // the loads before them do not wait for these too.
-    const int rec_blk = upd ? a_prev / R::NB : 0, rec_slot = upd ? a_prev % R::NB : 0;
+    const int rec_blk = fold ? a_prev / R::NB : 0, rec_slot = fold ? a_prev % R::NB : 0;
     const uint32_t rec_main = (uint32_t)(rec_blk * R::BLK + rec_slot * R::MAIN);
     const uint32_t rec_tail = (uint32_t)(rec_blk * R::BLK + R::NB * R::MAIN + rec_slot * R::TAIL - R::MAIN);
     auto rec_at = [&](int c) { return (uint32_t)c + (c < R::MAIN ? rec_main : rec_tail); };
-    const bool gathers = NW == 1 || (wave > 0 && (wave - 1) * kWave < R::R);
+    const bool gathers = FOLD && (NW == 1 || (wave > 0 && (wave - 1) * kWave < R::R));
     if (gathers) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -794,7 +845,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         }
         if (p.keep_stats && wave == u0 / kWave) {
             // (its two words: lanes past 1 repeat the second)
-            const int *st = reinterpret_cast<const int *>(p.stats + (size_t)inst * K + (upd ? a_upd : 0));
+            const int *st = reinterpret_cast<const int *>(p.stats + (size_t)inst * K + (fold ? a_upd : 0));
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(st + (lane < 1 ? 0 : 1)),
                                              (__attribute__((address_space(3))) void *)s_stu, 4, 0, 0);
         }
@@ -861,7 +912,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         }
         if (lane < D) {
             s_x[lane] = x_lane;
-            s_xp[lane] = xp_word;
+            if constexpr (FOLD) s_xp[lane] = xp_word;
         }
     }
 
@@ -979,14 +1030,17 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // Active arms other than the one being updated, in index order: 64 arms at
     // a time, the two mask words taken to scalar registers, each arm placed by
     // the count of active lanes below it.  The updated arm, if in play, takes
-    // the slot after them: it is scored from LDS.
+    // the slot after them: it is scored from LDS, or, folded in ahead of this
+    // kernel, like the other arms, except that an exploiting instance still
+    // sums its theta terms in the record's order.
+    const int a_own = FOLD ? a_upd : greedy && upd ? a_prev : -1;
     int nlist = 0, upd_in = 0;
     if (wave == 0) {
         if (!x_ok) word = 0u;
         if (lane == KW - 1 && (K & 31) != 0) word &= (1u << (K & 31)) - 1u;
-        if (upd) {
-            upd_in = (int)((uint32_t)__builtin_amdgcn_readlane((int)word, a_upd >> 5) >> (a_upd & 31) & 1u);
-            if (lane == a_upd >> 5) word &= ~(1u << (a_upd & 31));
+        if (a_own >= 0) {
+            upd_in = (int)((uint32_t)__builtin_amdgcn_readlane((int)word, a_own >> 5) >> (a_own & 31) & 1u);
+            if (lane == a_own >> 5) word &= ~(1u << (a_own & 31));
         }
         for (int k0 = 0; k0 < K; k0 += kWave) {
             // (lanes past the last word hold zeros)
@@ -997,7 +1051,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
                 s_list[nlist + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))] = (short)(k0 + lane);
             nlist += __popcll(bal);
         }
-        if (upd_in && lane == 0) s_list[nlist] = (short)a_upd;
+        if (upd_in && lane == 0) s_list[nlist] = (short)a_own;
         if (NW > 1 && lane == 0) s_nlist = nlist | upd_in << 16;
     }
     if constexpr (NW > 1) {
@@ -1022,7 +1076,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // pass is scored while the next one's loads are in flight: the lane's
     // main chunks, then its three tail floats.  The first pass is issued now,
     // beside the previous record, so that the two round trips are one.
-    float4 buf_a[S], buf_b[S];
+    float4 buf_a[S], buf_b[S], buf_more[NBUF > 2 ? NBUF - 2 : 1][S];
     const char *rec_bytes = reinterpret_cast<const char *>(recs);
     auto fetch = [&](int slot, float4 *dst) {
         if (slot >= nlist) return;
@@ -1061,7 +1115,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             // the loads to LDS have landed (gfx9 encoding: vmcnt 0 only)
             __builtin_amdgcn_s_waitcnt(0x0F70);
         }
-        __syncthreads();
+        if constexpr (FOLD) __syncthreads();
     };
 
     // ---- square-root rank-1 update of the previous decision's arm ----
@@ -1070,7 +1124,9 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // whenever the whole list fits in the first pass), in LDS; the updated
     // record is written back as the kernel's last act (write_back below).
     auto update = [&]() {
-        if (upd) {
+        // (fused and separate products as written, here and in agft_update_kernel)
+#pragma clang fp contract(off)
+        if (fold) {
             // Lane l of every wavefront takes column j = l % D of one row per
             // pass (row segments of D lanes; a pass of the workgroup covers RP
             // rows), so that the column sums and the row prefix sums below are
@@ -1103,9 +1159,10 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             }
             // alpha_j = 1 + f_0^2 + ... + f_j^2 (prefix over the segment) and the
             // column coefficients of M; alpha_{d-1} from the segment's last lane
-            const float incl = segment_scan<D>(fj * fj, lane);
+            const float f2 = fj * fj;
+            const float incl = segment_scan<D>(fj, fj, f2, lane);
             const float al = 1.0f + incl;
-            const float al_prev = 1.0f + (incl - fj * fj);
+            const float al_prev = 1.0f + (incl - f2);
             const float ca = sqrtf(al_prev / al), cb = fj / sqrtf(al_prev * al);
             const float al_last = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), D - 1));
             // prediction error r - xp^T theta
@@ -1126,8 +1183,8 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
                 const int pos = pos_S(ps, i < D ? i : 0);
                 const float sij = in_row ? s_old[pos] : 0.0f;
                 const float q = fj * sij;
-                const float qi = segment_scan<D>(q, lane);
-                if (in_row) s_new[pos] = ca * sij - cb * (qi - q);
+                const float qi = segment_scan<D>(fj, sij, q, lane);
+                if (in_row) s_new[pos] = fmaf(ca, sij, -(cb * (qi - q)));
                 if (i < D && jc == D - 1) {
                     const int tp = tbase + ps * TF * (RP / 2);
                     s_new[tp] = fmaf(qi * inv_al, err, s_old[tp]);
@@ -1137,7 +1194,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             if constexpr (TF == 4)
                 if (tid < G) s_new[4 * R::MAIN + 4 * tid + 3] = 0.0f;
             __syncthreads();
-        } else if (has_prev && tid == 0) {
+        } else if (has_prev && !upd && tid == 0) {
             blk[kInstBad] += 1;
         }
     };
@@ -1148,7 +1205,7 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
     // so stores in the middle of the step would hold up the rest of it by
     // their full latency.
     auto write_back = [&]() {
-        if (upd) {
+        if (fold) {
             if (gathers) {
                 float4 *dst = p.arms + (size_t)inst * inst_chunks;
 #pragma unroll
@@ -1223,6 +1280,9 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
             }
         };
         theta_fetch(0);
+        float2 own = make_float2(0.0f, 0.0f);
+        if (!FOLD && upd_in && wave == 0)
+            own = *reinterpret_cast<const float2 *>(th_bytes + (uint32_t)a_own * (D * 4) + t % G * 8);
         record_ready();
         update();
         const float4 x4 = s_x4[jt];
@@ -1241,9 +1301,12 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         if (upd_in && wave == 0) {
             const int jg = t % G;
             const float2 xt = reinterpret_cast<const float2 *>(s_x)[jg];
-            const float *tl = s_new + 4 * R::MAIN + TF * jg;
-            const float m = group_sum<G>(fmaf(tl[2], xt.y, tl[1] * xt.x));
-            if (lane == 0) s_sc[a_upd] = make_float2(m, 0.0f);
+            if constexpr (FOLD) {
+                const float *tl = s_new + 4 * R::MAIN + TF * jg;
+                own = make_float2(tl[1], tl[2]);
+            }
+            const float m = group_sum<G>(fmaf(own.y, xt.y, own.x * xt.x));
+            if (lane == 0) s_sc[a_own] = make_float2(m, 0.0f);
         }
     } else {
         if (streams) fetch(grp, buf_a);
@@ -1252,6 +1315,20 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         // ---- scoring of every listed arm (Eq. 1), two passes in flight ----
         if (streams) {
             selectors();
+            if constexpr (!FOLD) {
+                fetch(apw + grp, buf_b);
+                for (int u = 2; u < NBUF; ++u) fetch(u * apw + grp, buf_more[u - 2]);
+                for (int base = 0;;) {
+                    score(buf_a, base + grp);
+                    score(buf_b, base + apw + grp);
+                    for (int u = 2; u < NBUF; ++u) score(buf_more[u - 2], base + u * apw + grp);
+                    base += NBUF * apw;
+                    if (base >= total) break;
+                    fetch(base + grp, buf_a);
+                    fetch(base + apw + grp, buf_b);
+                    for (int u = 2; u < NBUF; ++u) fetch(base + u * apw + grp, buf_more[u - 2]);
+                }
+            } else
             for (int base = 0;;) {
                 if (base + apw < nlist) fetch(base + apw + grp, buf_b);
                 score(buf_a, base + grp);
@@ -1499,6 +1576,168 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
         if constexpr (ENV) agft_env_detail::env_epilogue(env, inst, a, lane, env_pre, s_envw);
     }
     if (NW == 1 || !by_list) write_back();
+}
+
+template <int D, int TF, int W, int NW, bool ENV>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ENV && D == 16 && W > 6 ? W - 1 : W)))
+void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
+    step_body<D, TF, NW, ENV, true>(p, env);
+}
+
+// The step after agft_update_kernel: it only reads the records.  An instance
+// has two passes' loads in flight together, three for the four-wavefront
+// d = 16 launch of four workgroups per compute unit, which leaves the
+// registers for it (K=128 d=16 B=65,536, us per step with the update: 745 with
+// two, 737 with three or four; 713 + 24 is what the traffic alone takes).
+template <int D, int TF, int W, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 16 && W == 6 && NW == 4 ? 5 : W)))
+void agft_score_kernel(StepArgs p) {
+    step_body<D, TF, NW, false, false, D == 16 && W == 6 && NW == 4 ? 3 : 2>(p, agft_env_detail::EnvArgs{});
+}
+
+// Folds every instance's previous reward into its arm, ahead of the score
+// kernel.  A wavefront takes 64/D instances, one per segment of D lanes: lane
+// j of a segment holds column j of the factor, so the chain of square roots
+// and divisions is worked out once for all of them, and each row of S' is one
+// segment prefix sum.  The operations and their order are those of the step
+// kernel's own update for workgroups of ORDER wavefronts, so the results are
+// the same bits.  Bound by the round trips to the instance's words and then to
+// its record, and by HBM: 65,536 instances at d = 16 take 24 us (80 MB of
+// records read and written), 16,384 take 8.6 us.
+constexpr int kUpdateThreads = 256;
+template <int D, int TF, int ORDER>
+__global__ __launch_bounds__(kUpdateThreads) void agft_update_kernel(StepArgs p) {
+#pragma clang fp contract(off)
+    using R = Rec<D, TF>;
+    constexpr int G = R::G, NI = kWave / D, WV = kUpdateThreads / kWave;
+    constexpr int NQ = (NI * R::R + kWave - 1) / kWave;   // loads of 64 chunks per wavefront
+    __shared__ float4 s_rec4[WV][NQ * kWave];
+    __shared__ float4 s_xp4[WV][NI][D / 4];
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int jc = lane % D, seg = lane / D;
+    const int i0 = (blockIdx.x * WV + wave) * NI;
+    if (i0 >= p.B) return;
+    const int inst = i0 + seg < p.B ? i0 + seg : p.B - 1;   // (past the end: repeats the last, stores nothing)
+    const int K = p.K;
+    const size_t inst_chunks = (size_t)((K + R::NB - 1) / R::NB) * R::BLK;
+    int32_t *blk = p.inst + (size_t)inst * p.IW;
+    const int a_prev = blk[kInstAprev];
+    const float xp = reinterpret_cast<const float *>(blk)[kInstX + jc];
+    const float r = p.reward[inst];
+    const bool upd = i0 + seg < p.B && a_prev >= 0 && a_prev < K && isfinite(r);
+    const int a = upd ? a_prev : 0;
+    const int rec_main = a / R::NB * R::BLK + a % R::NB * R::MAIN;
+    const int rec_tail = a / R::NB * R::BLK + R::NB * R::MAIN + a % R::NB * R::TAIL - R::MAIN;
+    // chunk q of the wavefront's NI records, in LDS order
+    auto place = [&](int q) {
+        const int s = q / R::R, c = q - s * R::R;
+        const int m = __shfl(rec_main, s * D), t = __shfl(rec_tail, s * D);
+        const size_t at = (size_t)(i0 + s < p.B ? i0 + s : p.B - 1) * inst_chunks;
+        return at + (uint32_t)(c + (c < R::MAIN ? m : t));
+    };
+    size_t at[NQ];
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const int q = u * kWave + lane;
+        at[u] = place(q < NI * R::R ? q : NI * R::R - 1);
+        load_to_lds<D>(p.arms + at[u], s_rec4[wave] + u * kWave);
+    }
+    int2 st = make_int2(0, 0);
+    if (p.keep_stats && jc == 0) st = p.stats[(size_t)inst * K + a];
+    reinterpret_cast<float *>(s_xp4[wave][seg])[jc] = xp;
+    // the records have landed (gfx9 encoding: vmcnt 0 only), and the wavefront's
+    // LDS writes are seen by its other lanes
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    auto lds_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    lds_order();
+
+    float *rec = reinterpret_cast<float *>(s_rec4[wave] + seg * R::R);
+    // column jc, rows 0..jc: top down in slice jc, or bottom up in slice D-1-jc,
+    // where row 0 is the tail float
+    const bool first = jc < G;
+    const int sl = first ? jc : D - 1 - jc;
+    auto pos = [&](int i) {
+        const int e = first ? i : D - i;
+        return e < D ? 4 * ((e >> 2) * G + sl) + (e & 3) : 4 * R::MAIN + TF * sl;
+    };
+    float col[D], xr[D];
+#pragma unroll
+    for (int q = 0; q < D / 4; ++q) {
+        const float4 v = s_xp4[wave][seg][q];
+        xr[4 * q] = v.x;
+        xr[4 * q + 1] = v.y;
+        xr[4 * q + 2] = v.z;
+        xr[4 * q + 3] = v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) col[i] = i <= jc ? rec[pos(i)] : 0.0f;
+    // f_j = sum_{i<=j} S_ij xp_i: chains of rows RP apart, summed as the lanes
+    // and wavefronts of the step kernel's update sum them
+    constexpr int SEGS = kWave / D, RP = ORDER * SEGS;
+    float fj = 0.0f;
+#pragma unroll
+    for (int w = 0; w < ORDER; ++w) {
+        float part[SEGS];
+#pragma unroll
+        for (int g = 0; g < SEGS; ++g) {
+            part[g] = 0.0f;
+#pragma unroll
+            for (int i = w * SEGS + g; i < D; i += RP) part[g] = fmaf(col[i], xr[i], part[g]);
+        }
+#pragma unroll
+        for (int h = 1; h < SEGS; h *= 2)
+#pragma unroll
+            for (int g = 0; g + h < SEGS; g += 2 * h) part[g] += part[g + h];
+        fj = w == 0 ? part[0] : fj + part[0];
+    }
+    const float f2 = fj * fj;
+    const float incl = segment_scan<D>(fj, fj, f2, lane);
+    const float al = 1.0f + incl;
+    const float al_prev = 1.0f + (incl - f2);
+    const float ca = sqrtf(al_prev / al), cb = fj / sqrtf(al_prev * al);
+    const float al_last = __shfl(al, lane | (D - 1));
+    const int tpos = 4 * R::MAIN + TF * (jc >> 1) + 1 + (jc & 1);
+    const float theta = rec[tpos];
+    float pred = group_sum<D < 16 ? D : 16>(xp * theta);
+    if constexpr (D == 32) pred = across<16>(pred, [](float x, float y) { return x + y; });
+    const float err = r - pred;
+    const float inv_al = 1.0f / al_last;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        const float q = fj * col[i];
+        const float qi = segment_scan<D>(fj, col[i], q, lane);
+        if (i <= jc) rec[pos(i)] = fmaf(ca, col[i], -(cb * (qi - q)));
+        col[i] = qi;
+    }
+    // the rows' totals, which the segment's last lane holds: (S f)_i
+    if (jc == D - 1) {
+#pragma unroll
+        for (int q = 0; q < D / 4; ++q)
+            s_xp4[wave][seg][q] = make_float4(col[4 * q], col[4 * q + 1], col[4 * q + 2], col[4 * q + 3]);
+    }
+    lds_order();
+    const float gain = reinterpret_cast<const float *>(s_xp4[wave][seg])[jc];
+    const float theta_new = fmaf(gain * inv_al, err, theta);
+    rec[tpos] = theta_new;
+    lds_order();
+    const unsigned long long upd_lanes = __ballot(upd);
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+        const int q = u * kWave + lane;
+        const int s = q / R::R;
+        if (q < NI * R::R && ((upd_lanes >> (s * D)) & 1ull) != 0) {
+            const float4 v = s_rec4[wave][q];
+            __builtin_nontemporal_store(nt_f4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt_f4 *>(p.arms + at[u]));
+        }
+    }
+    if (upd && p.theta != nullptr) p.theta[((size_t)inst * K + a) * D + jc] = theta_new;
+    if (upd && p.keep_stats && jc == 0)
+        p.stats[(size_t)inst * K + a] = make_int2(st.x + 1, __float_as_int(__int_as_float(st.y) + r));
 }
 
 // ---- initialisation and export ----
@@ -1854,6 +2093,27 @@ void launch_width(int waves, int cap, unsigned grid, size_t lds, hipStream_t str
     }
 }
 
+// The score kernel, likewise.
+template <int D, int TF, int W>
+void launch_score(int waves, int cap, unsigned grid, size_t lds, hipStream_t stream, const StepArgs &p) {
+    if (waves == 1) {
+        hipLaunchKernelGGL((agft_score_kernel<D, TF, W, 1>), dim3(grid), dim3(kWave), lds, stream, p);
+    } else {
+        static std::atomic<int64_t> cache[kMaxDevices];
+        lds = capped_lds(reinterpret_cast<const void *>(&agft_score_kernel<D, TF, W, 4>), 4 * kWave, lds, cap, cache);
+        hipLaunchKernelGGL((agft_score_kernel<D, TF, W, 4>), dim3(grid), dim3(4 * kWave), lds, stream, p);
+    }
+}
+
+// The update on its own, for the order of sums of workgroups of `waves`.
+template <int D, int TF>
+void launch_update(int waves, hipStream_t stream, const StepArgs &p) {
+    constexpr int per_group = kUpdateThreads / D;
+    const dim3 grid((unsigned)(((int64_t)p.B + per_group - 1) / per_group)), block(kUpdateThreads);
+    if (waves == 1) hipLaunchKernelGGL((agft_update_kernel<D, TF, 1>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((agft_update_kernel<D, TF, 4>), grid, block, 0, stream, p);
+}
+
 // One decision for every instance of handle h (and, with env, the
 // environment's response): arguments checked by the caller.
 int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32_t *d_action, float *d_scores,
@@ -1916,9 +2176,19 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     // (K=128 d=16, us per fused step, uncapped / at 4, measured when larger
     // batches took the single launch too: B=65,536 881.5 / 891.0, B=16,384
     // 211.9 / 218.0).
-    const int cap = env != nullptr ? 0 : cu_workgroups_for(waves, shape.simd_waves);
-#define AGFT_LAUNCH(D_, TF_, W_)                                                       \
-    (env != nullptr ? launch_width<D_, TF_, W_, true>(waves, cap, grid, lds, s, p, e) \
+    const int cap = env != nullptr ? 0 : cu_workgroups_for(c, waves, shape.simd_waves);
+    const int score_cap = cu_workgroups_for(c, score_waves_at(c, t), shape.simd_waves);
+    // the update ahead of the step, where that pays (never for the simulator's
+    // single launch, whose batches are small, nor for a flush)
+    const bool split = env == nullptr && h->pending && d_ctx != nullptr && split_update(c);
+    const int score_waves = score_waves_at(c, t);
+    if (split) {
+        for_layout(c.d, shape.tail_floats, [&](auto dc, auto tf) { launch_update<dc.value, tf.value>(waves, s, p); });
+        if (hipGetLastError() != hipSuccess) return AGFT_E_HIP;
+    }
+#define AGFT_LAUNCH(D_, TF_, W_)                                                          \
+    (env != nullptr ? launch_width<D_, TF_, W_, true>(waves, cap, grid, lds, s, p, e)    \
+     : split        ? launch_score<D_, TF_, W_>(score_waves, score_cap, grid, lds, s, p) \
                     : launch_width<D_, TF_, W_, false>(waves, cap, grid, lds, s, p, e))
     switch (c.d) {
         case 8:
@@ -2068,7 +2338,7 @@ int agft_launch_shape_for(const agft_config *cfg, agft_launch_shape *out) {
     out->tail_floats = tail_floats(*cfg);
     out->simd_waves = occupancy_for(*cfg, out->tail_floats);
     out->early_update = early_update(*cfg) ? 1 : 0;
-    out->cu_workgroups = cu_workgroups_for(out->waves, out->simd_waves);
+    out->cu_workgroups = cu_workgroups_for(*cfg, out->waves, out->simd_waves);
     return AGFT_OK;
 }
 

@@ -1,0 +1,73 @@
+"""Large batches fold the previous rewards in with a kernel of their own ahead
+of the step; small ones in the step kernel.  Instances are independent, so a
+large batch's instances, run again as a small batch, have to end in the same
+state, bit for bit: models, masks, instance words, statistics and theta copies,
+and to take the same actions and report the same scores at every step."""
+import pytest
+import torch
+
+from gpu_helpers import say
+from paper_2508_01744_amd import Tuner
+
+pytestmark = pytest.mark.gpu
+
+RULES = dict(ext_rounds=60, ext_min_n=2, ext_thr=-1.2, hist_after=5, hist_min_n=2, hist_kappa=1.0, hist_min_arms=3,
+             cascade_k=3)
+SWITCH = dict(ph_delta=0.05, ph_lambda=2.0, ph_window=8, ph_min_rounds=10)
+WINDOW = dict(refine_period=7, refine_stride=3, refine_half=10, refine_mature=15, refine_min_n=1)
+OPTIONS = {
+    "plain": dict(),
+    "pruning": dict(prune_rule=1, prune_period=9),
+    "rules": dict(prune_rule=15, prune_period=9, heuristics=RULES),
+    "switch": dict(prune_rule=1, prune_period=9, exploit=SWITCH),
+    "all": dict(prune_rule=15, prune_period=9, heuristics=RULES, exploit=SWITCH, refine=WINDOW),
+    "reevaluated": dict(prune_rule=1, prune_period=9, prune_sticky=0, refine=WINDOW),
+}
+
+
+def _split(B, K, d, opts):
+    """The host rule, restated: enough instances, and a stream past the cache."""
+    play = K if "refine" not in opts else min(K, max((K - 1) // 3 + 1, 21))
+    return B >= (16384 if d == 32 else 8192) and B * play * 4 * (d + d * (d + 1) // 2) >= (512 if d == 8 else 256) << 20
+
+
+# (B, K, d): one- and four-wavefront workgroups, ragged last blocks and last
+# wavefronts of instances, K past one ballot
+SIZES = [(8195, 55, 16), (8192, 130, 16), (33001, 21, 16), (8193, 373, 8), (70003, 45, 8), (16387, 9, 32), (16385, 31, 32)]
+
+
+@pytest.mark.parametrize("name", sorted(OPTIONS))
+@pytest.mark.parametrize("B,K,d", SIZES)
+def test_large_batch_is_its_instances(B, K, d, name):
+    opts = OPTIONS[name]
+    if not _split(B, K, d, opts):
+        pytest.skip("below the size that takes the separate update")
+    n, T = 70, 24
+    rows = torch.cat([torch.arange(6), torch.arange(B // 2, B // 2 + 32), torch.arange(B - 32, B)]).cuda()
+    say(f"[split] {name} B={B} K={K} d={d}")
+    big, few = Tuner(B, K, d, alpha0=0.5, **opts), Tuner(n, K, d, alpha0=0.5, **opts)
+    g = torch.Generator(device="cuda").manual_seed(B + K + d)
+    sc_big, sc_few = torch.empty(B, 2, K, device="cuda"), torch.empty(n, 2, K, device="cuda")
+    r = None
+    for t in range(T):
+        x = torch.randn(B, d, generator=g, device="cuda")
+        x[:, 0] = 1.0
+        if t == 6:
+            x[B - 1, 1] = float("nan")
+        dump = t % 5 == 2
+        a = big.step(x, r, scores=sc_big if dump else None)
+        b = few.step(x[rows].contiguous(), None if r is None else r[rows].contiguous(), scores=sc_few if dump else None)
+        assert torch.equal(a[rows], b), t
+        if dump:
+            assert torch.equal(sc_big[rows], sc_few), t
+        r = torch.randn(B, generator=g, device="cuda") * 0.3 - (0.9 if t < T // 2 else 1.5)
+        if t == 9:
+            r[0], r[B - 2] = float("inf"), float("nan")
+    for step in ("pending", "flushed"):
+        if step == "flushed":
+            big.flush(r)
+            few.flush(r[rows].contiguous())
+        u, v = big.view(), few.view()
+        for key in ("arms", "mask", "inst", "stats", "theta"):
+            if u[key] is not None:
+                assert torch.equal(u[key][rows].contiguous().view(torch.uint8), v[key].contiguous().view(torch.uint8)), (step, key)
