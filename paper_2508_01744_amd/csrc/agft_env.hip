@@ -13,7 +13,12 @@
 #include "agft_env_math.h"
 
 namespace agft_env_detail {
-constexpr int kEnvThreads = 256;
+// One wavefront per workgroup, so that a small batch spreads over the compute
+// units: a launch is little more than its own latency and one chain of a load
+// round trip and the logarithms.  Measured on MI355X (us per launch, 256 / 64
+// threads): B=1,024 d=32 4.44 / 3.66, B=4,096 d=8 3.44 / 3.25, B=16,384 d=16
+// 4.00 / 3.67, B=65,536 d=16 5.94 / 5.87.
+constexpr int kEnvThreads = 64;
 
 // One thread per instance.  Each context goes through LDS so that the
 // block's contexts (contiguous in the output) leave as whole-line float4
