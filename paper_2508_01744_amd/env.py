@@ -49,6 +49,8 @@ class GpuEnv:
         self.ctx = torch.empty(self.B, self.d, dtype=torch.float32, device=dev)
         self.reward = torch.empty(self.B, dtype=torch.float32, device=dev)
         self.stream = stream if stream is not None else torch.cuda.current_stream(dev)
+        lib = L.lib()
+        self._agft_env_step, self._agft_sim_step = lib.agft_env_step, lib.agft_sim_step
 
     def _s(self):
         return ctypes.c_void_p(self.stream.cuda_stream)
@@ -60,10 +62,12 @@ class GpuEnv:
         return self.ctx
 
     def step(self, t, action):
-        L.check("agft_env_step", L.agft_env_step(self.cfg, _ptr(self.state), self.nbytes, int(t),
-                                                 _ptr(action), _ptr(self.arrivals),
-                                                 _ptr(self.noise), _ptr(self.reward),
-                                                 _ptr(self.ctx), self._s()))
+        code = self._agft_env_step(ctypes.byref(self.cfg), self.state.data_ptr(), self.nbytes, int(t),
+                                   None if action is None else action.data_ptr(), self.arrivals.data_ptr(),
+                                   self.noise.data_ptr(), self.reward.data_ptr(), self.ctx.data_ptr(),
+                                   self.stream.cuda_stream)
+        if code != L.AGFT_OK:
+            L.check("agft_env_step", code)
         return self.reward, self.ctx
 
     def fused_step(self, tuner, action, scores=None):
@@ -73,7 +77,10 @@ class GpuEnv:
         r_{t-1} on entry and x_{t+1} and r_t on return."""
         tuner._check(action, (self.B,), torch.int32)
         tuner._check(scores, (self.B, 2, tuner.K), torch.float32)
-        L.check("agft_sim_step", L.agft_sim_step(tuner.h, self.cfg, _ptr(self.state), self.nbytes,
-                                                 _ptr(self.arrivals), _ptr(self.noise), _ptr(self.ctx),
-                                                 _ptr(self.reward), _ptr(action), _ptr(scores)))
+        code = self._agft_sim_step(tuner.h, ctypes.byref(self.cfg), self.state.data_ptr(), self.nbytes,
+                                   self.arrivals.data_ptr(), self.noise.data_ptr(), self.ctx.data_ptr(),
+                                   self.reward.data_ptr(), None if action is None else action.data_ptr(),
+                                   None if scores is None else scores.data_ptr())
+        if code != L.AGFT_OK:
+            L.check("agft_sim_step", code)
         return self.reward, self.ctx

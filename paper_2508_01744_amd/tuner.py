@@ -79,6 +79,10 @@ class Tuner:
         code, h = L.agft_create(self.cfg, _ptr(state), state.numel(), _stream_handle(self.stream))
         L.check("agft_create", code)
         self.h = h
+        # what every step needs, worked out once: a small batch's step on the
+        # GPU takes no longer than the host's part of the call
+        self._agft_step = L.lib().agft_step
+        self._shapes = (self.B, self.d), (self.B,), (self.B, 2, self.K)
 
     @classmethod
     def from_workload(cls, wl, B=None, **kw):
@@ -103,7 +107,7 @@ class Tuner:
             return
         if t.device != self.device or t.dtype != dtype or not t.is_contiguous():
             raise ValueError(f"expected a contiguous {dtype} tensor on {self.device}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:   # (torch.Size is a tuple)
             raise ValueError(f"expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
     def step(self, ctx, reward=None, action=None, scores=None):
@@ -112,14 +116,19 @@ class Tuner:
         ctx [B][d] fp32, reward [B] fp32 (None before the first decision),
         action [B] int32 out (allocated if None), scores [B][2][K] fp32 out or None.
         """
-        self._check(ctx, (self.B, self.d), torch.float32)
-        self._check(reward, (self.B,), torch.float32)
+        per_ctx, per_instance, per_arm = self._shapes
+        self._check(ctx, per_ctx, torch.float32)
+        self._check(reward, per_instance, torch.float32)
         if action is None:
             action = torch.empty(self.B, dtype=torch.int32, device=self.device)
-        self._check(action, (self.B,), torch.int32)
-        self._check(scores, (self.B, 2, self.K), torch.float32)
-        L.check("agft_step", L.agft_step(self.h, _ptr(ctx), _ptr(reward), _ptr(action),
-                                         _ptr(scores)))
+        else:
+            self._check(action, per_instance, torch.int32)
+        self._check(scores, per_arm, torch.float32)
+        code = self._agft_step(self.h, None if ctx is None else ctx.data_ptr(),
+                               None if reward is None else reward.data_ptr(), action.data_ptr(),
+                               None if scores is None else scores.data_ptr())
+        if code != L.AGFT_OK:
+            L.check("agft_step", code)
         return action
 
     def flush(self, reward):
