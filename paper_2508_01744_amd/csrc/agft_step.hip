@@ -345,7 +345,7 @@ bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <=
 // that the Infinity Cache (256 MB) holds.  Measured on MI355X (us per step, in
 // one kernel / two):
 //   K=128 d=16: B=2,048 28.0 / 29.9, 4,096 53.3 / 52.3, 8,192 103.0 / 98.1,
-//     16,384 200 / 187, 65,536 795 / 737; with the refinement (21 arms) B=8,192
+//     16,384 200 / 187, 65,536 795 / 717; with the refinement (21 arms) B=8,192
 //     25.8 / 27.6, 16,384 47.3 / 46.5, 32,768 91.2 / 87.3, 65,536 179 / 170;
 //     mostly exploiting B=4,096 24.0 / 26.5, 8,192 45.8 / 44.9, 65,536 297 / 267;
 //     rules 2-8 B=4,096 60.6 / 60.6, 16,384 210 / 194
@@ -519,6 +519,20 @@ template <int D>
 __device__ __forceinline__ void st_record(float4 *p, float x, float y, float z, float w) {
     if constexpr (D == 16) __builtin_nontemporal_store(nt_f4{x, y, z, w}, reinterpret_cast<nt_f4 *>(p));
     else *p = make_float4(x, y, z, w);
+}
+
+// One word of an instance block.  THROUGH: written through the caches at once
+// (a store visible to the whole device), not left in them to be evicted
+// between the reads of a stream, which costs more: 65,536 lines of 128 bytes
+// beside a 5.1 GB stream take 38 us so left and 11 us written through.  Used by
+// the score kernel's four-wavefront workgroups, whose streams are long
+// (measured on MI355X, us per step, left / through: K=128 d=16 B=65,536 736 /
+// 716; with four arms left in play, B=16,384, 63 / 65), not by one-wavefront
+// ones (with the refinement, B=65,536, 171 / 172).
+template <bool THROUGH>
+__device__ __forceinline__ void st_word(int32_t *p, int32_t v) {
+    if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
 }
 
 // Element `idx` of a register array indexed by a lane-varying value
@@ -853,7 +867,7 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
 
     // Page-Hinkley test on the instance's rewards and the switch to greedy
     // exploitation (uniform scalar code, single precision, fixed order).
-    static_assert(kInstMode == 3 && kInstPh == 4 && kInstPhLast == 10 && kInstPhMargin == 11 && kInstLo == 12 &&
+    static_assert(kInstAprev == 0 && kInstKact == 1 && kInstMode == 3 && kInstPh == 4 && kInstPhLast == 10 && kInstPhMargin == 11 && kInstLo == 12 &&
                       kInstHi == 13 && kInstStride == 14,
                   "word order of the instance block");
     int mode = p.e.on ? wa.w : -1;
@@ -1552,8 +1566,8 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
                 p.hdr->pending = 1;
             }
         }
-        if (lane == kInstAprev) blk[kInstAprev] = a;
-        if (lane == kInstKact) blk[kInstKact] = cnt;
+        constexpr bool kThrough = !FOLD && NW == 4;
+        if (lane <= kInstKact) st_word<kThrough>(blk + lane, lane == kInstAprev ? a : cnt);
         if (sc != nullptr && lane == kInstGap) {
             float t1 = top1, t2 = top2;   // one wavefront: already merged in every lane
             if constexpr (NW > 1) {
@@ -1568,9 +1582,9 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
         }
         if (anchor >= 0 && lane >= kInstLo && lane <= kInstStride)
             blk[lane] = lane == kInstLo ? nlo : (lane == kInstHi ? nhi : 1);
-        if (ph_lane) blk[tid] = s_phw[tid - kInstMode];
+        if (ph_lane) st_word<kThrough>(blk + tid, s_phw[tid - kInstMode]);
         if (lane >= kInstX && lane < kInstX + D)
-            reinterpret_cast<float *>(blk)[lane] = s_x[lane - kInstX];
+            st_word<kThrough>(blk + lane, __float_as_int(s_x[lane - kInstX]));
         // the context and reward read at the start are dead by now: the
         // environment's response overwrites them in place
         if constexpr (ENV) agft_env_detail::env_epilogue(env, inst, a, lane, env_pre, s_envw);
@@ -1587,8 +1601,8 @@ void agft_step_kernel(StepArgs p, agft_env_detail::EnvArgs env) {
 // The step after agft_update_kernel: it only reads the records.  An instance
 // has two passes' loads in flight together, three for the four-wavefront
 // d = 16 launch of four workgroups per compute unit, which leaves the
-// registers for it (K=128 d=16 B=65,536, us per step with the update: 745 with
-// two, 737 with three or four; 713 + 24 is what the traffic alone takes).
+// registers for it (K=128 d=16 B=65,536, us per step with the update, before
+// st_word's stores: 745 with two, 737 with three or four).
 template <int D, int TF, int W, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 16 && W == 6 && NW == 4 ? 5 : W)))
 void agft_score_kernel(StepArgs p) {
