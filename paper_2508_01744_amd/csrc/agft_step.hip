@@ -1765,6 +1765,15 @@ struct InitArgs {
     float inv_sqrt_lambda;
 };
 
+// A launch takes fewer than 2^32 threads per dimension of its grid, which a
+// buffer past 68 GB exceeds at one chunk per thread: workgroups beyond kRow
+// take further rows, the last of them part-filled.
+constexpr unsigned kRow = 1u << 23;
+dim3 rows_of(size_t groups) {
+    return groups <= kRow ? dim3((unsigned)groups) : dim3(kRow, (unsigned)((groups + kRow - 1) / kRow));
+}
+__device__ __forceinline__ uint64_t row_group() { return (uint64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Record chunks per workgroup of the initialisation.
 constexpr int kInitThreads = 256, kInitChunks = kInitThreads;
 
@@ -1786,12 +1795,14 @@ __global__ __launch_bounds__(kInitThreads) void agft_init_kernel(InitArgs p) {
     const uint32_t KB = (uint32_t)(p.K + R::NB - 1) / R::NB;
     const uint64_t chunks = (uint64_t)p.B * KB * R::BLK;
     const int tail_arms = p.K % R::NB;   // arms of an instance's last block, if part-filled
-    const uint64_t c0 = (uint64_t)blockIdx.x * kInitChunks;
+    const uint64_t group = row_group();
+    const uint64_t c0 = group * kInitChunks;
     const uint64_t blk0 = c0 / R::BLK;
     const uint32_t o0 = (uint32_t)(c0 - blk0 * R::BLK);
     const uint32_t kb0 = (uint32_t)(blk0 % KB);
     float4 *arms = reinterpret_cast<float4 *>(p.base + p.lay.arms) + c0;
-    const uint32_t left = chunks - c0 < (uint64_t)kInitChunks ? (uint32_t)(chunks - c0) : (uint32_t)kInitChunks;
+    const uint32_t left = c0 >= chunks ? 0u
+                        : chunks - c0 < (uint64_t)kInitChunks ? (uint32_t)(chunks - c0) : (uint32_t)kInitChunks;
 #pragma unroll
     for (int q = 0; q < kInitChunks / kInitThreads; ++q) {
         const uint32_t c = (uint32_t)(q * kInitThreads + tid);
@@ -1805,8 +1816,8 @@ __global__ __launch_bounds__(kInitThreads) void agft_init_kernel(InitArgs p) {
         if (c < left) *reinterpret_cast<nt_f4 *>(arms + c) = v;
     }
 
-    const uint64_t gtid = (uint64_t)blockIdx.x * kInitThreads + tid;
-    const uint64_t gsz = (uint64_t)gridDim.x * kInitThreads;
+    const uint64_t gtid = group * kInitThreads + tid;
+    const uint64_t gsz = (uint64_t)gridDim.x * gridDim.y * kInitThreads;
     // masks, every arm in play, and the gaps before and after them
     const uint32_t KW = (uint32_t)(p.K + 31) / 32;
     const uint32_t last = p.K % 32 ? (1u << (p.K % 32)) - 1u : 0xffffffffu;
@@ -1862,7 +1873,8 @@ __global__ __launch_bounds__(kExportThreads) void agft_export_kernel(const float
     const int tid = threadIdx.x;
     const uint32_t KB = (uint32_t)(K + R::NB - 1) / R::NB;
     const uint64_t nblk = (uint64_t)B * KB;
-    const uint64_t blk0 = (uint64_t)blockIdx.x * BW;
+    const uint64_t blk0 = row_group() * BW;
+    if (blk0 >= nblk) return;
     const int nch = (int)(nblk - blk0 < (uint64_t)BW ? nblk - blk0 : (uint64_t)BW) * R::BLK;
     const float4 *src = arms + blk0 * R::BLK;
 #pragma unroll
@@ -2287,7 +2299,7 @@ int agft_create(const agft_config *cfg, void *d_state, size_t nbytes, void *stre
     a.stride0 = cfg->refine ? cfg->refine_stride : 1;
     a.inv_sqrt_lambda = (float)(1.0 / std::sqrt((double)cfg->lambda));
     const size_t chunks = (size_t)cfg->B * instance_chunks(cfg->K, cfg->d, want.tail_floats);
-    const dim3 grid((unsigned)((chunks + kInitChunks - 1) / kInitChunks)), block(kInitThreads);
+    const dim3 grid = rows_of((chunks + kInitChunks - 1) / kInitChunks), block(kInitThreads);
     for_layout(cfg->d, want.tail_floats, [&](auto d, auto tf) {
         hipLaunchKernelGGL((agft_init_kernel<d.value, tf.value>), grid, block, 0, h->stream, a);
     });
@@ -2385,7 +2397,7 @@ int agft_export(agft_handle *h, float *d_theta, float *d_ainv) {
         constexpr int D = d.value, TF = tf.value;
         constexpr int arms_per_wg = kExportThreads / (D / 4 * (D / 4)), blocks_per_wg = arms_per_wg / Rec<D, TF>::NB;
         const size_t blocks = (size_t)c.B * (size_t)((c.K + Rec<D, TF>::NB - 1) / Rec<D, TF>::NB);
-        hipLaunchKernelGGL((agft_export_kernel<D, TF>), dim3((unsigned)((blocks + blocks_per_wg - 1) / blocks_per_wg)),
+        hipLaunchKernelGGL((agft_export_kernel<D, TF>), rows_of((blocks + blocks_per_wg - 1) / blocks_per_wg),
                            dim3(kExportThreads), 0, h->stream, arms, c.B, c.K, d_theta, d_ainv);
     });
     return hip_status(hipGetLastError());

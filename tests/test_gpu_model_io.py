@@ -89,6 +89,23 @@ def test_export_is_the_records_product(B, K, d, prune):
         assert torch.equal(whole[1:-1], want.reshape(-1)) and whole[0] == 7.0 and whole[-1] == 7.0
 
 
+def test_buffers_past_one_row_of_workgroups():
+    """76 GB of models (more than 2^32 chunks): set up, and theta exported, to
+    the last instance, in launches of more than one row of workgroups."""
+    B, K, d = 33001, 1021, 32   # 1.005 rows of the export's workgroups, 2.2 of the set-up's
+    few = Tuner(3, K, d)
+    t = Tuner(B, K, d)
+    say(f"[rows] {t.nbytes / 1e9:.1f} GB")
+    assert B * ((K + 1) // 2) > 2 << 23   # two blocks of two arms per workgroup
+    u, v = t.view(), few.view()
+    for key in ("arms", "mask", "inst"):
+        for at in (0, B // 2, B - 3):
+            assert torch.equal(u[key][at:at + 3], v[key]), (key, at)
+    u["arms"][B - 3:].normal_(generator=torch.Generator(device="cuda").manual_seed(3))
+    v["arms"].copy_(u["arms"][B - 3:])
+    assert torch.equal(t.export(theta=True, ainv=False)[0][B - 3:], few.export(theta=True, ainv=False)[0])
+
+
 def test_export_keeps_infinities_to_their_entries():
     """An infinite factor element reaches the products that hold it and no other."""
     B, K, d = 3, 9, 16
