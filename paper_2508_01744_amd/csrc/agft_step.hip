@@ -354,8 +354,12 @@ bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <=
 //   d=32, whose update is the longest: K=256 B=2,048 183 / 186, 4,096 374 / 362,
 //     with a quarter of the arms in play B=2,615 69.1 / 77.3; K=128 B=5,231 252 /
 //     243 and 74.5 / 81.9; K=32 B=20,926 269 / 264 and 122 / 106
-bool split_update(const agft_config &c) {
+// With the score dump, whose stores interfere either way, not for streams up to
+// 16 KB either (us per step, in one kernel / two): refinement B=65,536 185 / 187,
+// K=45 d=16 (27 KB) 362 / 329, K=128 d=16 887 / 800, mostly exploiting 309 / 301.
+bool split_update(const agft_config &c, bool dump) {
     const size_t stream = (size_t)c.B * explore_bytes(c);
+    if (dump && explore_bytes(c) <= 16384) return false;
     return c.B >= (c.d == 32 ? 16384 : 8192) && stream >= (size_t)(c.d == 8 ? 512 : 256) << 20;
 }
 
@@ -521,14 +525,17 @@ __device__ __forceinline__ void st_record(float4 *p, float x, float y, float z, 
     else *p = make_float4(x, y, z, w);
 }
 
-// One word of an instance block.  THROUGH: written through the caches at once
+// One word of an instance block or of the score dump.  THROUGH: written through the caches at once
 // (a store visible to the whole device), not left in them to be evicted
 // between the reads of a stream, which costs more: 65,536 lines of 128 bytes
 // beside a 5.1 GB stream take 38 us so left and 11 us written through.  Used by
 // the score kernel's four-wavefront workgroups, whose streams are long
 // (measured on MI355X, us per step, left / through: K=128 d=16 B=65,536 736 /
 // 716; with four arms left in play, B=16,384, 63 / 65), not by one-wavefront
-// ones (with the refinement, B=65,536, 171 / 172).
+// ones (with the refinement, B=65,536, 171 / 172).  The score kernel's dump goes
+// through at both widths (us per step with the dump, and the gap word, left /
+// through): K=128 d=16 B=65,536 951 / 800, B=16,384 243 / 210, K=64 d=32
+// B=20,000 520 / 492, K=45 d=16 B=65,536 335 / 329, K=130 d=8 B=65,536 331 / 320.
 template <bool THROUGH>
 __device__ __forceinline__ void st_word(int32_t *p, int32_t v) {
     if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1463,8 +1470,8 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
             }
         }
         if (sc != nullptr && k < K) {
-            sc[k] = u;
-            sc[K + k] = act ? s_sc[k].y : -INFINITY;
+            st_word<!FOLD>(reinterpret_cast<int32_t *>(sc + k), __float_as_int(u));
+            st_word<!FOLD>(reinterpret_cast<int32_t *>(sc + K + k), __float_as_int(act ? s_sc[k].y : -INFINITY));
         }
         if (prune_now) {
             // clear the arms rule 1 removed from the global words (non-sticky:
@@ -1578,7 +1585,7 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
                 t2 = fmaxf(fminf(t1, s_top[w][0]), fmaxf(t2, s_top[w][1]));
                 t1 = fmaxf(t1, s_top[w][0]);
             }
-            blk[kInstGap] = __float_as_int(t1 - t2);   // +inf with one kept arm
+            st_word<kThrough>(blk + kInstGap, __float_as_int(t1 - t2));   // +inf with one kept arm
         }
         if (anchor >= 0 && lane >= kInstLo && lane <= kInstStride)
             blk[lane] = lane == kInstLo ? nlo : (lane == kInstHi ? nhi : 1);
@@ -2206,7 +2213,7 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     const int score_cap = cu_workgroups_for(c, score_waves_at(c, t), shape.simd_waves);
     // the update ahead of the step, where that pays (never for the simulator's
     // single launch, whose batches are small, nor for a flush)
-    const bool split = env == nullptr && h->pending && d_ctx != nullptr && split_update(c);
+    const bool split = env == nullptr && h->pending && d_ctx != nullptr && split_update(c, d_scores != nullptr);
     const int score_waves = score_waves_at(c, t);
     if (split) {
         for_layout(c.d, shape.tail_floats, [&](auto dc, auto tf) { launch_update<dc.value, tf.value>(waves, s, p); });
