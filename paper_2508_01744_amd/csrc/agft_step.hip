@@ -490,6 +490,7 @@ struct StepArgs {
     int32_t prune_reset;   // rule 1 starts again from the whole action space (non-sticky)
     int32_t early_update;  // fold the previous reward in before the stream
     int32_t keep_stats;    // maintain the per-arm reward counts and sums
+    int32_t sum_waves;     // workgroup width whose order of sums a step after a separate update keeps (1 or 4)
     float alpha;
     int64_t t_next;        // t after this call (header bookkeeping)
 };
@@ -944,10 +945,30 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
         const int2 *st = p.stats + (size_t)inst * K;
         const Heuristics &h = p.h;
         auto act0 = [&](int k) { return ((s_mask[k >> 5] >> (k & 31)) & 1u) != 0; };
+        // The mean and the spread over the arms are sums in single precision, and
+        // the last bit of sigma can decide on an arm: they are taken in the order
+        // of workgroups of `order` wavefronts whatever this kernel's width, so
+        // that a separate update, which changes the width of what follows it,
+        // removes the same arms.  Turn v stands for wavefronts v*NW .. v*NW+NW-1.
+        const int order = FOLD || NW > 1 ? NW : p.sum_waves;
+        auto fsum = [](float a, float b) { return a + b; };
+        auto fmx = [](float a, float b) { return fmaxf(a, b); };
+        auto isum = [](int a, int b) { return a + b; };
+        auto imx = [](int a, int b) { return a > b ? a : b; };
+        auto sum_arms = [&](auto term) {
+            float total = 0.0f;
+            for (int v0 = 0; v0 < K && v0 < order * kWave; v0 += nthr) {
+                float part = 0.0f;
+                for (int k = v0 + tid; k < K; k += order * kWave) part = term(k, part);
+                part = block_reduce(part, s_red_v, lane, wave, nwave, fsum);
+                total = v0 == 0 ? part : total + part;
+            }
+            return total;
+        };
         // counts (as int bits) and means to s_sc, which the stream rewrites
         int q = 0;
-        float qsum = 0.0f, qbest = -INFINITY;
-        for (int k = tid; k < K; k += nthr) {
+        float qbest = -INFINITY;
+        const float qsum = sum_arms([&](int k, float part) {
             const int2 v = st[k];
             int n = v.x;
             float rs = __int_as_float(v.y);
@@ -957,29 +978,22 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
             }
             const float mean = n > 0 ? rs / (float)n : 0.0f;
             s_sc[k] = make_float2(__int_as_float(n), mean);
-            if (act0(k) && n >= h.hist_min_n) {
-                ++q;
-                qsum += mean;
-                qbest = fmaxf(qbest, mean);
-            }
-        }
-        auto fsum = [](float a, float b) { return a + b; };
-        auto fmx = [](float a, float b) { return fmaxf(a, b); };
-        auto isum = [](int a, int b) { return a + b; };
-        auto imx = [](int a, int b) { return a > b ? a : b; };
+            const bool counts = act0(k) && n >= h.hist_min_n;
+            q += counts ? 1 : 0;
+            qbest = counts ? fmaxf(qbest, mean) : qbest;
+            return counts ? part + mean : part;
+        });
         q = block_reduce(q, s_red_n, lane, wave, nwave, isum);
-        qsum = block_reduce(qsum, s_red_v, lane, wave, nwave, fsum);
         qbest = block_reduce(qbest, s_red_v, lane, wave, nwave, fmx);
         const bool hist_on = (h.mask & 4) && p.t >= h.hist_after && q >= h.hist_min_arms && q > 0;
         float sigma = 0.0f;
         if (hist_on) {
             const float mu = qsum / (float)q;
-            float acc = 0.0f;
-            for (int k = tid; k < K; k += nthr) {
+            const float acc = sum_arms([&](int k, float part) {
                 const int n = __float_as_int(s_sc[k].x);
-                if (act0(k) && n >= h.hist_min_n) acc += (s_sc[k].y - mu) * (s_sc[k].y - mu);
-            }
-            acc = block_reduce(acc, s_red_v, lane, wave, nwave, fsum);
+                const float dev = s_sc[k].y - mu;
+                return act0(k) && n >= h.hist_min_n ? fmaf(dev, dev, part) : part;
+            });
             sigma = sqrtf(acc / (float)q);
         }
         auto gone = [&](int k) {
@@ -2197,6 +2211,7 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     const int waves = waves_at(c, t);
     p.early_update = shape.early_update;
     p.keep_stats = stats_kept(c) ? 1 : 0;
+    p.sum_waves = waves;
     if (waves != 1 && waves != 4) return AGFT_E_UNSUPPORTED;
     const unsigned grid = (unsigned)c.B;
     const size_t lds = step_lds_bytes(c.K);

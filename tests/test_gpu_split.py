@@ -3,6 +3,7 @@ of the step; small ones in the step kernel.  Instances are independent, so a
 large batch's instances, run again as a small batch, have to end in the same
 state, bit for bit: models, masks, instance words, statistics and theta copies,
 and to take the same actions and report the same scores at every step."""
+import numpy as np
 import pytest
 import torch
 
@@ -71,3 +72,57 @@ def test_large_batch_is_its_instances(B, K, d, name):
         for key in ("arms", "mask", "inst", "stats", "theta"):
             if u[key] is not None:
                 assert torch.equal(u[key][rows].contiguous().view(torch.uint8), v[key].contiguous().view(torch.uint8)), (step, key)
+
+
+def _sum(x, waves):
+    """[n, K] summed over K in single precision as a workgroup of `waves`
+    wavefronts does: each thread its arms in turn, a tree over the 64 lanes of
+    a wavefront, then wavefront after wavefront."""
+    n, K = x.shape
+    p = np.zeros((n, -(-K // (64 * waves)), waves, 64), np.float32)
+    p.reshape(n, -1)[:, :K] = x
+    p = p.cumsum(1, dtype=np.float32)[:, -1]
+    while p.shape[2] > 1:
+        p = p[:, :, 0::2] + p[:, :, 1::2]
+    return p[:, :, 0].cumsum(1, dtype=np.float32)[:, -1]
+
+
+def _removed(mean, waves):
+    """The arms that rule 4 with kappa = 1 removes, [n, K]."""
+    K = np.float32(mean.shape[1])
+    dev = mean - (_sum(mean, waves) / K)[:, None]
+    sigma = np.sqrt(_sum(dev * dev, waves) / K)
+    return sigma[:, None] - (mean.max(1)[:, None] - mean) < 0
+
+
+@pytest.mark.parametrize("B,K,d", [(8192, 130, 16), (8193, 373, 8)])
+def test_reward_rule_at_its_threshold(B, K, d):
+    """Rule 4 removes an arm whose mean lies more than sigma below the best: with
+    one arm of every instance at that threshold, the last bit of sigma decides,
+    and with it the order of the sums.  A batch that takes the separate update
+    has to remove what its instances on their own do."""
+    n = 4096
+    rng = np.random.default_rng(K)
+    mean = (rng.standard_normal((n, K)) * 0.1 - 0.9).astype(np.float32)
+    best, at = mean.max(1).astype(np.float64), rng.integers(0, K, n)
+    at = np.where(mean[np.arange(n), at] == mean.max(1), (at + 1) % K, at)
+    for _ in range(30):   # (sigma moves by a fraction of what the one mean does)
+        mean[np.arange(n), at] = best - mean.astype(np.float64).std(1)
+    differ = (_removed(mean, 1) != _removed(mean, 4)).any(1).mean()
+    assert differ > 0.02   # the inputs tell one order from the other
+    say(f"[split] rule 4 at its threshold B={B} K={K} d={d}: one wavefront or four differ in {differ:.3f} of the instances")
+    opts = dict(prune_rule=4, heuristics=dict(hist_after=1, hist_min_n=2, hist_kappa=1.0, hist_min_arms=3))
+    assert _split(B, K, d, opts) and n < 8192
+    big, few = Tuner(B, K, d, **opts), Tuner(n, K, d, **opts)
+    x = torch.randn(B, d, generator=torch.Generator().manual_seed(K)).cuda()
+    big.step(x)
+    few.step(x[:n].contiguous())
+    rows = torch.arange(B) % n
+    for t, m in ((few, mean), (big, mean[rows])):
+        t.view()["stats"][..., 0] = 2
+        t.view()["stats"][..., 1] = torch.from_numpy(m * np.float32(2)).cuda().view(torch.int32)   # 2 rewards: an exact mean
+    r = torch.full((B,), float("nan"), device="cuda")   # (no update: the statistics stay as they are)
+    big.step(x, r)
+    few.step(x[:n].contiguous(), r[:n].contiguous())
+    wrong = (big.view()["mask"][:n] != few.view()["mask"]).any(1).float().mean().item()
+    assert wrong == 0.0, f"{wrong:.4f} of the instances"
