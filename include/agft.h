@@ -234,6 +234,11 @@ int agft_create(const agft_config *cfg, void *d_state, size_t nbytes, void *stre
  *           every arm active before this step's pruning, -inf for the others;
  *           with it the step also leaves the top-two gap of its decision in
  *           word 15 of each instance block (agft_state_view.inst).
+ * AGFT_E_HIP: no decision was made, t is what it was and the reward still
+ * counts as pending.  Call again with the same arguments, or flush: where the
+ * failed call had folded the reward in already (a step of two launches, below,
+ * whose second one failed), that is remembered, in the state buffer too, and it
+ * is not folded in again.
  */
 int agft_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32_t *d_action,
               float *d_scores);

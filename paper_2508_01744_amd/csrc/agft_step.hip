@@ -67,7 +67,10 @@ constexpr int kMaxWords = kMaxK / 32;
 constexpr int kMaxWaves = 16;
 constexpr size_t kAlign = 256;
 
-// Header at the start of the state buffer (256 bytes).
+// Header at the start of the state buffer (256 bytes).  pending: 0 no decision
+// awaits its reward, 1 one does, kPendingFolded between the two launches of a
+// step: the decision is pending, its reward already in its arm.
+constexpr int kPendingFolded = 2;
 struct alignas(16) StateHeader {
     uint32_t magic;
     uint32_t version;
@@ -1770,6 +1773,7 @@ __global__ __launch_bounds__(kUpdateThreads) void agft_update_kernel(StepArgs p)
             __builtin_nontemporal_store(nt_f4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt_f4 *>(p.arms + at[u]));
         }
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) p.hdr->pending = kPendingFolded;
     if (upd && p.theta != nullptr) p.theta[((size_t)inst * K + a) * D + jc] = theta_new;
     if (upd && p.keep_stats && jc == 0)
         p.stats[(size_t)inst * K + a] = make_int2(st.x + 1, __float_as_int(__int_as_float(st.y) + r));
@@ -1986,6 +1990,7 @@ struct agft_handle {
     hipStream_t stream;
     int64_t t;
     int pending;
+    int folded;   // 1: the pending reward is in its arm already, by a step whose update ran and whose score launch failed
 };
 
 namespace {
@@ -2152,13 +2157,16 @@ void launch_score(int waves, int cap, unsigned grid, size_t lds, hipStream_t str
     }
 }
 
-// The update on its own, for the order of sums of workgroups of `waves`.
+// The update on its own, for the order of sums of workgroups of `waves`; the
+// launch's own status.
 template <int D, int TF>
-void launch_update(int waves, hipStream_t stream, const StepArgs &p) {
+hipError_t launch_update(int waves, hipStream_t stream, StepArgs p) {
     constexpr int per_group = kUpdateThreads / D;
     const dim3 grid((unsigned)(((int64_t)p.B + per_group - 1) / per_group)), block(kUpdateThreads);
-    if (waves == 1) hipLaunchKernelGGL((agft_update_kernel<D, TF, 1>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((agft_update_kernel<D, TF, 4>), grid, block, 0, stream, p);
+    const void *kernel = waves == 1 ? reinterpret_cast<const void *>(&agft_update_kernel<D, TF, 1>)
+                                    : reinterpret_cast<const void *>(&agft_update_kernel<D, TF, 4>);
+    void *args[] = {&p};
+    return hipLaunchKernel(kernel, grid, block, args, 0, stream);
 }
 
 // One decision for every instance of handle h (and, with env, the
@@ -2227,12 +2235,17 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     const int cap = env != nullptr ? 0 : cu_workgroups_for(c, waves, shape.simd_waves);
     const int score_cap = cu_workgroups_for(c, score_waves_at(c, t), shape.simd_waves);
     // the update ahead of the step, where that pays (never for the simulator's
-    // single launch, whose batches are small, nor for a flush)
-    const bool split = env == nullptr && h->pending && d_ctx != nullptr && split_update(c, d_scores != nullptr);
+    // single launch, whose batches are small, nor for a flush); a step or flush
+    // that finds the reward folded in already only takes what follows the update
+    const bool split = env == nullptr && h->pending &&
+                       (h->folded || (d_ctx != nullptr && split_update(c, d_scores != nullptr)));
     const int score_waves = score_waves_at(c, t);
-    if (split) {
-        for_layout(c.d, shape.tail_floats, [&](auto dc, auto tf) { launch_update<dc.value, tf.value>(waves, s, p); });
-        if (hipGetLastError() != hipSuccess) return AGFT_E_HIP;
+    if (split && !h->folded) {
+        hipError_t ran = hipErrorUnknown;
+        for_layout(c.d, shape.tail_floats,
+                   [&](auto dc, auto tf) { ran = launch_update<dc.value, tf.value>(waves, s, p); });
+        if (ran == hipSuccess) h->folded = 1;
+        if (hipGetLastError() != hipSuccess || ran != hipSuccess) return AGFT_E_HIP;
     }
 #define AGFT_LAUNCH(D_, TF_, W_)                                                          \
     (env != nullptr ? launch_width<D_, TF_, W_, true>(waves, cap, grid, lds, s, p, e)    \
@@ -2256,6 +2269,7 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     }
 #undef AGFT_LAUNCH
     if (hipGetLastError() != hipSuccess) return AGFT_E_HIP;
+    h->folded = 0;
     if (d_ctx != nullptr) {
         h->t = t + 1;
         h->pending = 1;
@@ -2290,6 +2304,7 @@ int agft_create(const agft_config *cfg, void *d_state, size_t nbytes, void *stre
     h->stream = static_cast<hipStream_t>(stream);
     h->t = 0;
     h->pending = 0;
+    h->folded = 0;
     const StateHeader want = make_header(cfg);
     if (cfg->flags & AGFT_ADOPT_STATE) {
         StateHeader got;
@@ -2303,12 +2318,13 @@ int agft_create(const agft_config *cfg, void *d_state, size_t nbytes, void *stre
             got.d != want.d || got.chunks != want.chunks || got.tail_floats != want.tail_floats ||
             got.stats_kept != want.stats_kept ||
             got.exploit != want.exploit || got.t < 0 ||
-            (got.pending != 0 && got.pending != 1)) {
+            got.pending < 0 || got.pending > kPendingFolded) {
             delete h;
             return AGFT_E_STATE;
         }
         h->t = got.t;
-        h->pending = got.pending;
+        h->pending = got.pending != 0 ? 1 : 0;
+        h->folded = got.pending == kPendingFolded ? 1 : 0;
         *out = h;
         return AGFT_OK;
     }
@@ -2359,7 +2375,7 @@ int agft_sim_step(agft_handle *h, const agft_env_config *env_cfg, void *d_env, s
     // Measured on MI355X (us per simulator step over the whole horizon,
     // fused / two launches): K=128 d=16 B=65,536 879 / 814, B=16,384 211 /
     // 201; K=64 d=8 B=4,096 16.1 / 18.5; K=256 d=32 B=1,024 23.4 / 27.1.
-    if (h->cfg.B > kFusedMaxB) {
+    if (h->cfg.B > kFusedMaxB || h->folded) {
         const int64_t t = h->t;
         const int rc = launch_step(h, d_ctx, d_reward, d_action, d_scores, nullptr);
         if (rc != AGFT_OK) return rc;

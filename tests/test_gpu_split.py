@@ -126,3 +126,39 @@ def test_reward_rule_at_its_threshold(B, K, d):
     few.step(x[:n].contiguous(), r[:n].contiguous())
     wrong = (big.view()["mask"][:n] != few.view()["mask"]).any(1).float().mean().item()
     assert wrong == 0.0, f"{wrong:.4f} of the instances"
+
+
+@pytest.mark.parametrize("name,B,K,d", [("all", 8192, 130, 16), ("switch", 33001, 21, 16), ("rules", 16385, 31, 32)])
+def test_a_folded_reward_is_not_folded_again(name, B, K, d):
+    """A state buffer as it is between the two launches of a step, the models
+    updated and the header marked: a decision or a flush that goes on from it
+    ends where the whole step or flush does."""
+    opts = dict(alpha0=0.5, **OPTIONS[name])
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x, r = torch.randn(16, B, d, generator=g, device="cuda"), torch.randn(16, B, generator=g, device="cuda") * 0.3 - 0.9
+    t = Tuner(B, K, d, **opts)
+    a = t.step(x[0])
+    for i in range(1, 15):
+        a = t.step(x[i], r[i - 1])
+    before = t.state.clone()
+    say(f"[split] folded ahead, {name} B={B} K={K} d={d}")
+
+    def adopt(state):
+        return Tuner(B, K, d, state=state, adopt=True, **opts)
+
+    flushed = adopt(before.clone())
+    flushed.flush(r[14])
+    between = before.clone()
+    u, v = adopt(between).view(), flushed.view()
+    for key in ("arms", "stats", "theta"):
+        if u[key] is not None:
+            u[key].copy_(v[key])
+    between[:256].view(torch.int32)[7] = 2   # the header's pending word
+    for scores in (None, torch.empty(B, 2, K, device="cuda")):
+        whole, rest = adopt(before.clone()), adopt(between.clone())
+        assert rest.view()["pending"] == 1
+        assert torch.equal(whole.step(x[15], r[14], scores=scores), rest.step(x[15], r[14], scores=scores))
+        assert torch.equal(whole.state, rest.state)
+    rest = adopt(between)
+    rest.flush(r[14])
+    assert torch.equal(rest.state, flushed.state)
