@@ -732,6 +732,19 @@ int cu_workgroups_for(const agft_config &c, int waves, int simd_waves) {
     return waves == 4 && simd_waves == 6 && explore_bytes(c) > 65536 ? 4 : 0;
 }
 
+// The environment's arguments of the fused kernel, read again from the launch's
+// argument memory: what is read through this pointer cannot be loaded before
+// the point of the call, so that the epilogue's constants hold no scalar
+// registers through the stream.
+__device__ __forceinline__ const agft_env_detail::EnvArgs &env_args_again() {
+    typedef const char __attribute__((address_space(4))) *kernarg_ptr;
+    constexpr size_t align = alignof(agft_env_detail::EnvArgs);
+    constexpr size_t off = (sizeof(StepArgs) + align - 1) / align * align;   // the kernel's second argument
+    kernarg_ptr at = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const agft_env_detail::EnvArgs *)(at + off);
+}
+
 // What bounds the kernel: HBM's rate where a batch streams many bytes, else
 // one instance's chain of dependent phases and the instructions that it
 // issues, four cycles each whether vector or scalar (half to two thirds of
@@ -1416,7 +1429,7 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
         }
         if (ph_lane) blk[tid] = s_phw[tid - kInstMode];
         if constexpr (ENV)
-            if (wave == 0) agft_env_detail::env_epilogue(env, inst, -1, lane, env_pre, s_envw);
+            if (wave == 0) agft_env_detail::env_epilogue(env_args_again(), inst, -1, lane, env_pre, s_envw);
         write_back();
         return;
     }
@@ -1611,7 +1624,7 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
             st_word<kThrough>(blk + lane, __float_as_int(s_x[lane - kInstX]));
         // the context and reward read at the start are dead by now: the
         // environment's response overwrites them in place
-        if constexpr (ENV) agft_env_detail::env_epilogue(env, inst, a, lane, env_pre, s_envw);
+        if constexpr (ENV) agft_env_detail::env_epilogue(env_args_again(), inst, a, lane, env_pre, s_envw);
     }
     if (NW == 1 || !by_list) write_back();
 }

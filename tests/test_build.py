@@ -31,6 +31,29 @@ def test_step_kernels_do_not_spill(tmp_path):
         assert scratch == 0, f"{name} spills {scratch} bytes per lane"
 
 
+@pytest.mark.skipif(not shutil.which(HIPCC) and not os.path.exists(HIPCC), reason="hipcc not found")
+def test_no_kernel_spills(tmp_path):
+    """Every kernel of the step's source: no scratch, no vector spill, and few
+    scalar registers spilled to lanes of vector ones (each costs a lane write and
+    a lane read of the few instructions that a small batch's step issues: with
+    64 to 101 of them the fused simulator step lost 6% at d = 8)."""
+    src = os.path.join(_build.CSRC, "agft_step.hip")
+    flags = [f for f in _build.HIPCC_FLAGS if f != "-shared"]
+    cmd = [HIPCC, *flags, "--cuda-device-only", "-c", "-I", _build.INCLUDE, src, "-o", str(tmp_path / "step.o"),
+           "-Rpass-analysis=kernel-resource-usage"]
+    out = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
+    kernels = re.findall(r"Function Name: (\S+)(.*?)(?=Function Name:|\Z)", out, re.S)
+    kinds = [re.search(r"agft_(\w+?)_kernel", name).group(1) for name, _ in kernels]
+    # (step: above; score and update: two widths or orders of each layout, d = 16
+    # packed scores at two register targets; set-up and export: each layout)
+    assert {k: kinds.count(k) for k in kinds} == dict(step=28, score=14, update=12, init=6, export=6)
+    for name, body in kernels:
+        scratch, scalar, vector = (int(re.search(p + r": (\d+)", body).group(1))
+                                   for p in (r"ScratchSize \[bytes/lane\]", "SGPRs Spill", "VGPRs Spill"))
+        assert scratch == 0 and vector == 0, f"{name} spills {scratch} bytes per lane"
+        assert scalar <= 32, f"{name} spills {scalar} scalar registers"
+
+
 def test_stream_ceiling_library_checks_its_arguments():
     """The bench's ceiling library is built beside the tuner's, exports its
     two entry points and rejects out-of-range arguments before any HIP call."""
