@@ -972,13 +972,14 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
         auto isum = [](int a, int b) { return a + b; };
         auto imx = [](int a, int b) { return a > b ? a : b; };
         auto sum_arms = [&](auto term) {
-            float total = 0.0f;
-            for (int v0 = 0; v0 < K && v0 < order * kWave; v0 += nthr) {
+            auto turn = [&](int v0) {
                 float part = 0.0f;
                 for (int k = v0 + tid; k < K; k += order * kWave) part = term(k, part);
-                part = block_reduce(part, s_red_v, lane, wave, nwave, fsum);
-                total = v0 == 0 ? part : total + part;
-            }
+                return block_reduce(part, s_red_v, lane, wave, nwave, fsum);
+            };
+            float total = turn(0);
+            if constexpr (!FOLD && NW == 1)
+                for (int v0 = nthr; v0 < K && v0 < order * kWave; v0 += nthr) total += turn(v0);
             return total;
         };
         // counts (as int bits) and means to s_sc, which the stream rewrites
