@@ -269,7 +269,7 @@ def measure(wl, K, W, dev, log_prefix="[bench]", draws=None):
     kernel_ms = np.array([a.elapsed_time(b) for a, b in ev])
 
     # the same steps through agft_sim_step (the environment in the step
-    # kernel's epilogue, one launch per step, up to 8,192 instances; the two
+    # kernel's epilogue, one launch per step, up to 3,072 instances; the two
     # kernels above)
     fresh()
     torch.cuda.synchronize()
@@ -540,7 +540,7 @@ def main():
         res["detail"]["workloads_note"] = ("each workload timed over its whole horizon from a fresh state, "
                                            "step and environment kernels, inputs resident; *_fused: the same "
                                            "steps through agft_sim_step (the environment in the step kernel's "
-                                           "epilogue, one launch per step, up to 8,192 instances; the step "
+                                           "epilogue, one launch per step, up to 3,072 instances; the step "
                                            "and environment kernels above); frac = algorithmic bytes per "
                                            "step-kernel launch over its average duration, of 8 TB/s; "
                                            "of_ceiling = the same rate over the stream ceiling's "

@@ -87,7 +87,7 @@ int agft_env_step(const agft_env_config *cfg, void *d_env, size_t nbytes, int32_
  *   agft_env_step(env_cfg, d_env, env_nbytes, t, d_action, d_arrivals, d_noise,
  *                 d_reward, d_ctx, stream of h);
  * with t the decisions h had made before the call (the decision step of
- * Sec. 4.2 followed by the measured window of Sec. 4.1).  Up to 8,192
+ * Sec. 4.2 followed by the measured window of Sec. 4.1).  Up to 3,072
  * instances in a single launch, each instance's environment running in the
  * step's epilogue once its decision is known, without the second launch and
  * its wait; beyond that as the two calls above, which are faster there.
@@ -98,6 +98,8 @@ int agft_env_step(const agft_env_config *cfg, void *d_env, size_t nbytes, int32_
  * device, non-NULL.  d_scores [B][2][K] or NULL, as in agft_step.
  * AGFT_E_INVAL for NULL or mismatched arguments, AGFT_E_STATE when the
  * exogenous draws end before this decision's window (t >= env_cfg->T).
+ * AGFT_E_HIP with t advanced: the decision was made and the second call's
+ * launch failed; that call is still to be made.
  */
 int agft_sim_step(agft_handle *h, const agft_env_config *env_cfg, void *d_env, size_t env_nbytes,
                   const int32_t *d_arrivals, const float *d_noise, float *d_ctx, float *d_reward,

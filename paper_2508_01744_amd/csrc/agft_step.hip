@@ -360,10 +360,11 @@ bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <=
 // With the score dump, whose stores interfere either way, not for streams up to
 // 16 KB either (us per step, in one kernel / two): refinement B=65,536 185 / 187,
 // K=45 d=16 (27 KB) 362 / 329, K=128 d=16 887 / 800, mostly exploiting 309 / 301.
+constexpr int kSplitMinB = 8192;   // (twice that at d = 32)
 bool split_update(const agft_config &c, bool dump) {
     const size_t stream = (size_t)c.B * explore_bytes(c);
     if (dump && explore_bytes(c) <= 16384) return false;
-    return c.B >= (c.d == 32 ? 16384 : 8192) && stream >= (size_t)(c.d == 8 ? 512 : 256) << 20;
+    return c.B >= (c.d == 32 ? 2 * kSplitMinB : kSplitMinB) && stream >= (size_t)(c.d == 8 ? 512 : 256) << 20;
 }
 
 // Workgroup width of the score kernel after a separate update: one wavefront
@@ -2087,7 +2088,8 @@ void for_layout(int d, int tf, Fn fn) {
 
 // agft_sim_step runs the environment in the step kernel's epilogue up to
 // this many instances, and launches the step and environment kernels above.
-constexpr int kFusedMaxB = 8192;
+constexpr int kFusedMaxB = 3072;
+static_assert(kFusedMaxB < kSplitMinB, "a batch in the single launch has no update of its own");
 
 // Dynamic LDS that caps a kernel at `cap` workgroups per compute unit: a
 // 1/cap share of the unit's LDS less the kernel's static LDS, lowered in
@@ -2386,10 +2388,17 @@ int agft_sim_step(agft_handle *h, const agft_env_config *env_cfg, void *d_env, s
     // Large batches take the step kernel and then the environment kernel:
     // there the epilogue's per-instance stores to the environment's
     // structure-of-arrays state cost more than the launch they save.
-    // Measured on MI355X (us per simulator step over the whole horizon,
-    // fused / two launches): K=128 d=16 B=65,536 879 / 814, B=16,384 211 /
-    // 201; K=64 d=8 B=4,096 16.1 / 18.5; K=256 d=32 B=1,024 23.4 / 27.1.
-    if (h->cfg.B > kFusedMaxB || h->folded) {
+    // Measured on MI355X (us per simulator step, fused / two launches, at
+    // B = 1,024, 3,072, 4,096 and 8,192):
+    //   d=8 K=64    8.4 / 9.7    12.3 / 12.9    15.3 / 14.7    27.6 / 24.5
+    //   d=8 K=200   11.7 / 13.6  26.0 / 26.2    33.5 / 32.2    62.5 / 56.4
+    //   d=16 K=128  17.3 / 18.0  42.6 / 45.1    58.6 / 57.7    110.8 / 102.7
+    //     the same with rules 2-8  18.8 / 20.0  47.2 / 47.7    62.2 / 59.5    115.9 / 108.9
+    //     with the refinement      9.6 / 11.7   12.7 / 14.6    15.3 / 16.2    28.9 / 28.5
+    //     mostly exploiting        15.6 / 17.5  19.1 / 20.3    21.7 / 22.0    35.4 / 36.6
+    //   d=32 K=256  42.1 / 44.3  116.8 / 116.3  155.7 / 153.1  307.2 / 301.9
+    //     late in a run            10.8 / 13.3  25.6 / 26.7    31.2 / 30.8    56.0 / 51.6
+    if (h->cfg.B > kFusedMaxB) {
         const int64_t t = h->t;
         const int rc = launch_step(h, d_ctx, d_reward, d_action, d_scores, nullptr);
         if (rc != AGFT_OK) return rc;

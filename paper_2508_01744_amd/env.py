@@ -72,7 +72,7 @@ class GpuEnv:
 
     def fused_step(self, tuner, action, scores=None):
         """One decision of tuner (agft_step) and this environment's response
-        to it (agft_sim_step: one launch up to 8,192 instances, the step and
+        to it (agft_sim_step: one launch up to 3,072 instances, the step and
         environment kernels above): self.ctx and self.reward hold x_t and
         r_{t-1} on entry and x_{t+1} and r_t on return."""
         tuner._check(action, (self.B,), torch.int32)

@@ -12,7 +12,7 @@ def run_closed_loop(wl, env_constants, arrivals, noise, T=None, probes=None, sco
 
     arrivals, noise: [T+1][B] (numpy or torch) exogenous draws.
     fused: each decision and the environment's response through
-    agft_sim_step (one launch up to 8,192 instances) instead of agft_step
+    agft_sim_step (one launch up to 3,072 instances) instead of agft_step
     and agft_env_step.
     probes: instance indices to record at every step (contexts, rewards,
     actions, masks, test words, action spaces; with scores, the scores and

@@ -80,7 +80,7 @@ int main(void)
 {
     agft_config c;
     memset(&c, 0, sizeof(c));
-    c.B = 8192;   /* the smallest batch that takes the separate update, and agft_sim_step's largest single launch */
+    c.B = 8192;   /* the smallest batch that takes the separate update */
     c.K = 128;
     c.d = 16;
     c.lambda = 1.0f;
@@ -149,7 +149,7 @@ int main(void)
     check(ne > 0, "environment configuration");
     start(0);
     check(agft_sim_step(h, &e, (void *)0x200000000ull, ne, (int32_t *)0x50000, (float *)0x60000, ctx, reward, action, NULL) ==
-              AGFT_OK && n_ran == 1, "simulator step: one launch");
+              AGFT_OK && n_ran == 3 && ran[0] == update && ran[1] == score, "simulator step: three launches");
     start(2);
     check(agft_step(h, ctx, reward, action, NULL) == AGFT_E_HIP, "score launch fails before a simulator step");
     start(0);

@@ -1,12 +1,13 @@
 """The simulator's fused step (agft_sim_step: the decision and the
-environment's response in one launch, up to 8,192 instances) against the two
+environment's response in one launch, up to 3,072 instances) against the two
 separate calls it replaces, and against the oracle.
 
 Fused and separate runs of the same workload must agree bit for bit:
 contexts, rewards, actions, masks, scores, top-two gaps and the final state
 buffer.  Full-size fused runs of the two workloads where the second launch
 weighs most (cfg1, cfg2) are also checked against the fp64 oracle and its
-environment like the separate runs."""
+environment like the separate runs, cfg2 at the most instances that the single
+launch takes too."""
 import ctypes
 
 import pytest
@@ -41,14 +42,16 @@ def test_fused_equals_separate(name):
     assert torch.equal(sep["env"].state, fus["env"].state)
 
 
-def test_large_batch_simulator_step_equals_separate():
-    """Above 8,192 instances agft_sim_step runs the step kernel and then the
+@pytest.mark.parametrize("B", [3072, 3073, 8193])
+def test_large_batch_simulator_step_equals_separate(B):
+    """Above 3,072 instances agft_sim_step runs the step kernel and then the
     environment kernel: the same results as the separate calls, bit for bit,
-    and the same in-place buffers (one instance past the threshold)."""
-    wl = get_workload("cfg3", B=8193, T=40)
-    say(f"[fused] two launches: {wl.name} B={wl.B} K={wl.K} d={wl.d} T={wl.T}")
+    and the same in-place buffers (both sides of the threshold, and with the
+    update a launch of its own)."""
+    wl = get_workload("cfg3", B=B, T=40)
+    say(f"[fused] {wl.name} B={wl.B} K={wl.K} d={wl.d} T={wl.T}")
     arr, noi = exogenous(wl)
-    ids = [0, 1, 4096, 8191, 8192]
+    ids = [0, 1, B // 2, B - 2, B - 1]
     sep = run_closed_loop(wl, ENV, arr, noi, probes=ids, scores=True)
     fus = run_closed_loop(wl, ENV, arr, noi, probes=ids, scores=True, fused=True)
     for key in sep["probes"]:
@@ -59,9 +62,9 @@ def test_large_batch_simulator_step_equals_separate():
     assert torch.equal(sep["env"].state, fus["env"].state)
 
 
-@pytest.mark.parametrize("name", ["cfg1", "cfg2"])
-def test_fused_full_size_parity(name):
-    wl = get_workload(name)
+@pytest.mark.parametrize("name,B", [("cfg1", None), ("cfg2", 3072), ("cfg2", None)])
+def test_fused_full_size_parity(name, B):
+    wl = get_workload(name) if B is None else get_workload(name, B=B)
     probes = probe_instances(wl.B, 64)
     say(f"[fused] parity {wl.name} B={wl.B} T={wl.T} probes={len(probes)}")
     arr, noi = exogenous(wl)
