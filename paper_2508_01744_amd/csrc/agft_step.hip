@@ -627,6 +627,35 @@ __device__ __forceinline__ BestPair wave_best(BestPair b) {
     return b;
 }
 
+// What N wavefronts of which wavefront w holds p_w sum to, worked out by one:
+// each part by wave_reduce's tree, then part after part.  The parts share the
+// tree's later levels, part w in the lanes w modulo N, for 13 (N = 2) and 21
+// (N = 4) instructions against 10 for one part and 20 and 40 apart (which cost
+// 2 us of a 47 us step, K=128 d=8 B=32,768 with eight arms left).
+template <int N>
+__device__ __forceinline__ float waves_sum(float p0, float p1, float p2, float p3, int lane) {
+    static_assert(N == 2 || N == 4, "two or four parts");
+    auto add = [](float a, float b) { return a + b; };
+    p0 += dpp<0xB1>(p0);             // quad_perm [1,0,3,2]
+    p1 += dpp<0xB1>(p1);
+    float v = lane & 1 ? p1 : p0;
+    v += dpp<0x4E>(v);               // quad_perm [2,3,0,1]
+    if constexpr (N == 4) {
+        p2 += dpp<0xB1>(p2);
+        p3 += dpp<0xB1>(p3);
+        float u = lane & 1 ? p3 : p2;
+        u += dpp<0x4E>(u);
+        v = lane & 2 ? u : v;
+    }
+    v += dpp<0x1B>(dpp<0x141>(v));   // the other quad of the half row, same place: mirrored, then each quad reversed
+    v += dpp<0x128>(v);              // row_ror:8, the other half row
+    v = across<16>(v, add);
+    v = across<32>(v, add);
+    float total = dpp<0x00>(v) + dpp<0x55>(v);                      // each quad's lanes 0, 1
+    if constexpr (N == 4) total = (total + dpp<0xAA>(v)) + dpp<0xFF>(v);   // 2, 3
+    return total;
+}
+
 // The arm of the wavefront's best pair: the largest value as an ordered
 // integer (negative floats with their magnitude bits flipped, -0 as +0), then
 // the smallest index that holds it.  Half the instructions of reducing pairs.
@@ -963,25 +992,33 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
         const Heuristics &h = p.h;
         auto act0 = [&](int k) { return ((s_mask[k >> 5] >> (k & 31)) & 1u) != 0; };
         // The mean and the spread over the arms are sums in single precision, and
-        // the last bit of sigma can decide on an arm: they are taken in the order
-        // of workgroups of `order` wavefronts whatever this kernel's width, so
-        // that a separate update, which changes the width of what follows it,
-        // removes the same arms.  Turn v stands for wavefronts v*NW .. v*NW+NW-1.
-        const int order = FOLD || NW > 1 ? NW : p.sum_waves;
+        // the last bit of sigma can decide on an arm: a step after a separate
+        // update takes them in the order of the one-launch step's width, whatever
+        // its own, and removes the same arms.
         auto fsum = [](float a, float b) { return a + b; };
         auto fmx = [](float a, float b) { return fmaxf(a, b); };
         auto isum = [](int a, int b) { return a + b; };
         auto imx = [](int a, int b) { return a > b ? a : b; };
         auto sum_arms = [&](auto term) {
-            auto turn = [&](int v0) {
-                float part = 0.0f;
-                for (int k = v0 + tid; k < K; k += order * kWave) part = term(k, part);
-                return block_reduce(part, s_red_v, lane, wave, nwave, fsum);
-            };
-            float total = turn(0);
-            if constexpr (!FOLD && NW == 1)
-                for (int v0 = nthr; v0 < K && v0 < order * kWave; v0 += nthr) total += turn(v0);
-            return total;
+            if constexpr (!FOLD && NW == 1) {
+                // (up to 64 arms the orders are the same)
+                if (p.sum_waves == 4 && K > kWave) {
+                    if (K <= 2 * kWave)
+                        return waves_sum<2>(term(lane, 0.0f), lane + kWave < K ? term(lane + kWave, 0.0f) : 0.0f, 0.0f,
+                                            0.0f, lane);
+                    float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, p3 = 0.0f;
+                    for (int k = lane; k < K; k += 4 * kWave) {
+                        p0 = term(k, p0);
+                        if (k + kWave < K) p1 = term(k + kWave, p1);
+                        if (k + 2 * kWave < K) p2 = term(k + 2 * kWave, p2);
+                        if (k + 3 * kWave < K) p3 = term(k + 3 * kWave, p3);
+                    }
+                    return waves_sum<4>(p0, p1, p2, p3, lane);
+                }
+            }
+            float part = 0.0f;
+            for (int k = tid; k < K; k += nthr) part = term(k, part);
+            return block_reduce(part, s_red_v, lane, wave, nwave, fsum);
         };
         // counts (as int bits) and means to s_sc, which the stream rewrites
         int q = 0;
