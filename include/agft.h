@@ -245,11 +245,14 @@ int agft_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32_t
 
 /* How agft_step launches the step kernel for cfg (host-only, no device
  * call): one workgroup per instance.  (At 8,192 instances or more, 16,384 at
- * d = 32, whose models in play fill 256 MB, 512 MB at d = 8, a decision with a
- * pending reward takes two launches: the update of every instance's arm, in
- * the order of sums of `waves`, then the step without it, whose workgroups
- * have one wavefront up to 32 KB streamed per instance, 96 KB with rules 2, 4
- * or 8, and four beyond.  The results are the same bits.)  The five fields follow from the
+ * d = 32, whose models in play fill 256 MB, a decision with a pending reward
+ * takes two launches: the update of every instance's arm, in the order of sums
+ * of `waves`, then the step without it, which streams the models and whose
+ * workgroups have one wavefront up to 32 KB streamed per instance, 96 KB with
+ * rules 2, 4 or 8, and four beyond, not `waves`.  At d = 8 the models have to fill
+ * 512 MB, without d_scores and with four wavefronts 2 GB; with d_scores and up
+ * to 16 KB streamed per instance it is one launch at any size.  The results are
+ * the same bits.)  The five fields follow from the
  * configuration alone: the bytes an exploring instance streams per step
  * (arms in play times 4(d + d(d+1)/2)) choose the record layout, with the
  * switch the bytes an exploiting instance streams choose the workgroup

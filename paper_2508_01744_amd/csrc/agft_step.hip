@@ -338,35 +338,6 @@ int waves_at(const agft_config &c, int64_t t) {
 // 220.8 us; K=256 d=32 B=1,024 92.4 / 91.7 us.
 bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <= 16384; }
 
-// Whether the update of the previous decisions' arms is a kernel of its own,
-// ahead of one that only reads the records.  A write-back between the reads of
-// a stream at HBM's rate costs far more than its bytes (65,536 of 608 bytes:
-// 97 us of a 810 us stream, against 24 us for all of them on their own; a
-// 16-byte-per-lane read-only stream of the same 5.1 GB takes 713 us), so large
-// batches that stream from HBM are better off with a second launch.  Not where
-// the launch costs more than the interference saves: few instances, or records
-// that the Infinity Cache (256 MB) holds.  Measured on MI355X (us per step, in
-// one kernel / two):
-//   K=128 d=16: B=2,048 28.0 / 29.9, 4,096 53.3 / 52.3, 8,192 103.0 / 98.1,
-//     16,384 200 / 187, 65,536 795 / 717; with the refinement (21 arms) B=8,192
-//     25.8 / 27.6, 16,384 47.3 / 46.5, 32,768 91.2 / 87.3, 65,536 179 / 170;
-//     mostly exploiting B=4,096 24.0 / 26.5, 8,192 45.8 / 44.9, 65,536 297 / 267;
-//     rules 2-8 B=4,096 60.6 / 60.6, 16,384 210 / 194
-//   K=64 d=8: B=16,384 (184 MB) 40.0 / 44.4, 32,768 (369 MB) 77.6 / 82.0,
-//     65,536 163 / 161; K=256 d=8: B=8,192 (369 MB) 65.6 / 68.2, 16,384 130 / 126
-//   d=32, whose update is the longest: K=256 B=2,048 183 / 186, 4,096 374 / 362,
-//     with a quarter of the arms in play B=2,615 69.1 / 77.3; K=128 B=5,231 252 /
-//     243 and 74.5 / 81.9; K=32 B=20,926 269 / 264 and 122 / 106
-// With the score dump, whose stores interfere either way, not for streams up to
-// 16 KB either (us per step, in one kernel / two): refinement B=65,536 185 / 187,
-// K=45 d=16 (27 KB) 362 / 329, K=128 d=16 887 / 800, mostly exploiting 309 / 301.
-constexpr int kSplitMinB = 8192;   // (twice that at d = 32)
-bool split_update(const agft_config &c, bool dump) {
-    const size_t stream = (size_t)c.B * explore_bytes(c);
-    if (dump && explore_bytes(c) <= 16384) return false;
-    return c.B >= (c.d == 32 ? 2 * kSplitMinB : kSplitMinB) && stream >= (size_t)(c.d == 8 ? 512 : 256) << 20;
-}
-
 // Workgroup width of the score kernel after a separate update: one wavefront
 // up to 32 KB per instance (96 KB with rules 2-8, which remove most arms in
 // the end), four beyond.  Without the update, an instance's chain is short and
@@ -376,12 +347,68 @@ bool split_update(const agft_config &c, bool dump) {
 // KB) 268 / 271 and 106 / 201, K=48 (29 KB) 256 / 243 and 94 / 144, K=64 (39
 // KB) 250 / 239 and 88 / 114, K=128 235 / 229 and 80 / 88; d=8 K=128 (23 KB)
 // 290 / 298 and 118 / 139, K=192 (34 KB) 281 / 270 and 116 / 121; d=32 K=20
-// (45 KB) 295 / 283 and 105 / 146.  With rules 2-8, K=128 d=16 B=16,384:
-// 193.6 / 195.1, with four arms in play 23.9 / 41.4.
+// (45 KB) 295 / 283 and 105 / 146.  With rules 2-8 one wavefront costs up to 4%
+// while every arm is in play and halves the step once eight are left; the line
+// lies where the former would make the step slower than one launch is (1.3 GB of
+// records, one wavefront / four / one launch, every arm in play, then eight):
+//   d=16 K=64 (38 KB)   220 / 228 / 250 and 63 / 129 / 174
+//        K=128 (76 KB)  218 / 212 / 224 and 40 / 70 / 93
+//        K=160 (95 KB)  217 / 211 / 224 and 34 / 59 / 77
+//        K=200 (119 KB) 220 / 210 / 222 and 33 / 50 / 64
+//        K=256 (152 KB) 219 / 209 / 217 and 30 / 42 / 52
+//   d=8  K=512 (88 KB)  246 / 247 / 253 and 49 / 72 / 94
+//        K=800 (138 KB) 263 / 248 / 254 and 57 / 61 / 79
+//   d=32 K=32 (70 KB)   253 / 254 / 266 and 92 / 138 / 167
+//        K=64 (140 KB)  418 / 390 / 407 and 87 / 127 / 153
 int score_waves_at(const agft_config &c, int64_t t) {
     const bool may_exploit = c.exploit && t >= c.ph_min_rounds;
     const size_t bytes = may_exploit ? (size_t)arms_in_play(c) * 4 * c.d : explore_bytes(c);
     return bytes <= (size_t)((c.prune_rule & 14) ? 96 : 32) * 1024 ? 1 : 4;
+}
+
+// Whether the update of the previous decisions' arms is a kernel of its own,
+// ahead of one that only reads the records.  A write-back between the reads of
+// a stream at HBM's rate costs far more than its bytes (65,536 of 608 bytes:
+// 97 us of a 810 us stream, against 24 us for all of them on their own; a
+// 16-byte-per-lane read-only stream of the same 5.1 GB takes 713 us), so large
+// batches that stream from HBM are better off with a second launch.  Not where
+// the launch costs more than the interference saves: few instances, or records
+// that the Infinity Cache (256 MB) holds.  At d = 8, whose records are smallest,
+// the gain is the second launch's width: with four wavefronts it is lost again
+// between all arms and few, so those batches need 2 GB.  The host does not know
+// how many arms are left: with a handful, two launches can cost up to 5 us more
+// than one, with all of them they gain 2-10%.  Measured on MI355X (us per step,
+// in one kernel / two, every arm in play, then a half, a quarter and eight):
+//   d=16 K=128: B=4,096 53.3 / 52.3; B=8,192 105 / 100, 69.2 / 61.9, 47.7 / 45.1,
+//     34.0 / 37.1; B=16,384 211 / 197, 135 / 114, 90.8 / 81.8, 65.8 / 66.8;
+//     B=65,536 819 / 746, 535 / 438, 354 / 306, 256 / 250; with the refinement
+//     (21 arms) B=8,192 25.8 / 27.6, 16,384 47.3 / 46.5, 65,536 179 / 170; mostly
+//     exploiting B=8,192 45.8 / 44.9, 65,536 297 / 267; rules 2-8 B=4,096 60.6 /
+//     60.6, 16,384 210 / 194
+//   d=16 K=64: B=8,192 58.5 / 57.0, 37.8 / 38.6, 28.6 / 31.3, 23.0 / 28.3;
+//     B=65,536 433 / 389, 273 / 245, 199 / 200
+//   d=8, one wavefront: K=64 B=16,384 (184 MB) 40.0 / 44.4, 65,536 163 / 161;
+//     K=128 B=32,768 (738 MB) 146 / 149, -, 82.8 / 63.8, 67.8 / 30.2; K=180
+//     B=17,000 (539 MB) 100 / 105, 69.4 / 69.7, 50.0 / 46.0, 38.4 / 20.2
+//   d=8, four: K=256 B=16,384 (738 MB) 131 / 133, 84.6 / 93.6, 56.8 / 61.7, 37.9 /
+//     38.0; 32,768 (1.5 GB) 268 / 261, 172 / 181, 111 / 117, 70.9 / 68.5; 65,536
+//     537 / 495, 349 / 355, 222 / 226, 140 / 130; K=373 B=32,768 (2.15 GB) 381 /
+//     366, 242 / 241, 153 / 160, 73.5 / 71.5
+//   d=32, whose update is the longest: K=256 B=2,048 183 / 186, 4,096 374 / 362,
+//     with a quarter of the arms B=2,615 69.1 / 77.3; K=32 B=16,384 211 / 213,
+//     127 / 129, 95 / 85, 80 / 74 (three); K=64 401 / 398, 219 / 223, 130 / 134,
+//     96 / 86; K=96 600 / 574, 318 / 318, 180 / 183, 97 / 88
+// With the score dump, whose stores interfere either way, not for streams up to
+// 16 KB (us per step, in one kernel / two): refinement B=65,536 185 / 187, K=45
+// d=16 (27 KB) 362 / 329, K=128 d=16 887 / 800, mostly exploiting 309 / 301; at
+// d = 8 beyond that from 512 MB at either width: K=256 B=16,384 154 / 152, 98.2 /
+// 102, 67.6 / 65.4, 56.4 / 53.5.
+constexpr int kSplitMinB = 8192;   // (twice that at d = 32)
+bool split_update(const agft_config &c, int64_t t, bool dump) {
+    const size_t stream = (size_t)c.B * explore_bytes(c);
+    if (dump && explore_bytes(c) <= 16384) return false;
+    const size_t least_mb = c.d != 8 ? 256 : dump || score_waves_at(c, t) == 1 ? 512 : 2048;
+    return c.B >= (c.d == 32 ? 2 * kSplitMinB : kSplitMinB) && stream >= least_mb << 20;
 }
 
 // What lane j of a group multiplies the positions of its record slice with.
@@ -2291,7 +2318,7 @@ int launch_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32
     // single launch, whose batches are small, nor for a flush); a step or flush
     // that finds the reward folded in already only takes what follows the update
     const bool split = env == nullptr && h->pending &&
-                       (h->folded || (d_ctx != nullptr && split_update(c, d_scores != nullptr)));
+                       (h->folded || (d_ctx != nullptr && split_update(c, t, d_scores != nullptr)));
     const int score_waves = score_waves_at(c, t);
     if (split && !h->folded) {
         hipError_t ran = hipErrorUnknown;

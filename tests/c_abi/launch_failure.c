@@ -1,66 +1,8 @@
 /*
  * What a step that takes two launches leaves when one of them fails.  Needs no
- * GPU: this program stands in for the HIP runtime's launch, error and copy
- * calls, so nothing runs, the kernels that the library asks for are counted
- * and told apart by their addresses, and any launch can be made to fail.
- * Test infrastructure only.
+ * GPU (hip_stub.h).  Test infrastructure only.
  */
-#include <stdint.h>
-#include <stdio.h>
-#include <string.h>
-
-#include <hip/hip_runtime_api.h>
-
-#include "agft.h"
-#include "agft_sim.h"
-
-static const void *ran[16];   /* kernels launched since the last start() */
-static int n_ran, fail_at;    /* fail_at: the launch that fails, from 1 (0: none) */
-static hipError_t last_error;
-static unsigned char header[256];   /* the state header that the library set up */
-
-/* (the compiler's launch syntax hands the launch's shape over through these) */
-static dim3 cfg_grid, cfg_block;
-static size_t cfg_lds;
-static hipStream_t cfg_stream;
-hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream)
-{
-    cfg_grid = grid, cfg_block = block, cfg_lds = lds, cfg_stream = stream;
-    return hipSuccess;
-}
-hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream)
-{
-    *grid = cfg_grid, *block = cfg_block, *lds = cfg_lds, *stream = cfg_stream;
-    return hipSuccess;
-}
-hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream)
-{
-    (void)grid, (void)block, (void)lds, (void)stream;
-    if (fail_at && --fail_at == 0) return last_error = hipErrorLaunchFailure;
-    if (n_ran < 16) ran[n_ran] = f;
-    ++n_ran;
-    const unsigned char *a = args[0];
-    for (int i = 0; f && i < 128; i += 4)   /* the set-up's arguments hold the header */
-        if (memcmp(a + i, "AGFT", 4) == 0) memcpy(header, a + i, sizeof(header));
-    return hipSuccess;
-}
-hipError_t hipGetLastError(void)
-{
-    const hipError_t e = last_error;
-    last_error = hipSuccess;
-    return e;
-}
-hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind kind, hipStream_t stream)
-{
-    (void)src, (void)kind, (void)stream;
-    memcpy(dst, header, n);
-    return hipSuccess;
-}
-hipError_t hipStreamSynchronize(hipStream_t stream)
-{
-    (void)stream;
-    return hipSuccess;
-}
+#include "hip_stub.h"
 
 static int fails;
 static void check(int ok, const char *what)
@@ -70,12 +12,6 @@ static void check(int ok, const char *what)
         ++fails;
     }
 }
-static void start(int fail)
-{
-    n_ran = 0;
-    fail_at = fail;
-}
-
 int main(void)
 {
     agft_config c;

@@ -26,24 +26,29 @@ OPTIONS = {
 }
 
 
-def _split(B, K, d, opts):
-    """The host rule, restated: enough instances, and a stream past the cache."""
+def _split(B, K, d, opts, dump=False):
+    """The host rule, restated (tests/test_launch_routes.py holds it against the
+    library's launches): enough instances, and a stream past the cache."""
     play = K if "refine" not in opts else min(K, max((K - 1) // 3 + 1, 21))
-    return B >= (16384 if d == 32 else 8192) and B * play * 4 * (d + d * (d + 1) // 2) >= (512 if d == 8 else 256) << 20
+    each = play * 4 * (d + d * (d + 1) // 2)
+    scored = play * 4 * d if "exploit" in opts else each   # (from the round of the first possible switch on)
+    wide = scored > (96 if opts.get("prune_rule", 0) & 14 else 32) << 10
+    least = 256 if d != 8 else 2048 if wide and not dump else 512
+    return B >= (16384 if d == 32 else 8192) and B * each >= least << 20 and not (dump and each <= 16384)
 
 
 # (B, K, d): one- and four-wavefront workgroups, ragged last blocks and last
 # wavefronts of instances, K past one ballot
-SIZES = [(8195, 55, 16), (8192, 130, 16), (33001, 21, 16), (8193, 373, 8), (70003, 45, 8), (16387, 9, 32), (16385, 31, 32)]
+SIZES = [(8195, 55, 16), (8192, 130, 16), (33001, 21, 16), (8193, 373, 8), (32769, 373, 8), (70003, 45, 8), (16387, 9, 32),
+         (16385, 31, 32)]
+CASES = [(*size, name) for size in SIZES for name in sorted(OPTIONS) if _split(*size, OPTIONS[name])]
+FEW = 70
 
 
-@pytest.mark.parametrize("name", sorted(OPTIONS))
-@pytest.mark.parametrize("B,K,d", SIZES)
+@pytest.mark.parametrize("B,K,d,name", CASES)
 def test_large_batch_is_its_instances(B, K, d, name):
     opts = OPTIONS[name]
-    if not _split(B, K, d, opts):
-        pytest.skip("below the size that takes the separate update")
-    n, T = 70, 24
+    n, T = FEW, 24
     rows = torch.cat([torch.arange(6), torch.arange(B // 2, B // 2 + 32), torch.arange(B - 32, B)]).cuda()
     say(f"[split] {name} B={B} K={K} d={d}")
     big, few = Tuner(B, K, d, alpha0=0.5, **opts), Tuner(n, K, d, alpha0=0.5, **opts)
