@@ -250,9 +250,10 @@ int agft_step(agft_handle *h, const float *d_ctx, const float *d_reward, int32_t
  * of `waves`, then the step without it, which streams the models and whose
  * workgroups have one wavefront up to 32 KB streamed per instance, 96 KB with
  * rules 2, 4 or 8, and four beyond, not `waves`.  At d = 8 the models have to fill
- * 512 MB, without d_scores and with four wavefronts 2 GB; with d_scores and up
- * to 16 KB streamed per instance it is one launch at any size.  The results are
- * the same bits.)  The five fields follow from the
+ * 512 MB; without d_scores 2 GB where those workgroups have four wavefronts, or,
+ * with no pruning rule, refinement or switch, 1 GB beyond 24 KB per instance.
+ * With d_scores and up to 16 KB streamed per instance it is one launch at any
+ * size.  The results are the same bits.)  The five fields follow from the
  * configuration alone: the bytes an exploring instance streams per step
  * (arms in play times 4(d + d(d+1)/2)) choose the record layout, with the
  * switch the bytes an exploiting instance streams choose the workgroup

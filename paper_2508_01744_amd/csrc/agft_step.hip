@@ -374,11 +374,12 @@ int score_waves_at(const agft_config &c, int64_t t) {
 // batches that stream from HBM are better off with a second launch.  Not where
 // the launch costs more than the interference saves: few instances, or records
 // that the Infinity Cache (256 MB) holds.  At d = 8, whose records are smallest,
-// the gain is the second launch's width: with four wavefronts it is lost again
-// between all arms and few, so those batches need 2 GB.  The host does not know
-// how many arms are left: with a handful, two launches can cost up to 5 us more
-// than one, with all of them they gain 2-10%.  Measured on MI355X (us per step,
-// in one kernel / two, every arm in play, then a half, a quarter and eight):
+// the gain is mostly the second launch's width: with four wavefronts it is lost
+// again between all arms and few, so where arms go those batches need 2 GB; where
+// none do, from 24 KB on, 1 GB.  The host does not know how many arms are left:
+// with a handful, two launches can cost up to 5 us more than one, with all of
+// them they gain 2-10%.  Measured on MI355X (us per step, in one kernel / two,
+// every arm in play, then a half, a quarter and eight):
 //   d=16 K=128: B=4,096 53.3 / 52.3; B=8,192 105 / 100, 69.2 / 61.9, 47.7 / 45.1,
 //     34.0 / 37.1; B=16,384 211 / 197, 135 / 114, 90.8 / 81.8, 65.8 / 66.8;
 //     B=65,536 819 / 746, 535 / 438, 354 / 306, 256 / 250; with the refinement
@@ -394,6 +395,9 @@ int score_waves_at(const agft_config &c, int64_t t) {
 //     38.0; 32,768 (1.5 GB) 268 / 261, 172 / 181, 111 / 117, 70.9 / 68.5; 65,536
 //     537 / 495, 349 / 355, 222 / 226, 140 / 130; K=373 B=32,768 (2.15 GB) 381 /
 //     366, 242 / 241, 153 / 160, 73.5 / 71.5
+//   d=8, no pruning: K=96 (17 KB) 0.55 GB 119 / 115, 1.1 GB 237 / 219; K=128 (23
+//     KB) 109 / 112, 218 / 214; K=160 (28 KB) 105 / 109, 211 / 211; K=180 (32 KB)
+//     103 / 107, 207 / 208; K=256 (45 KB) 0.7 GB 131 / 133, 1.5 GB 268 / 261
 //   d=32, whose update is the longest: K=256 B=2,048 183 / 186, 4,096 374 / 362,
 //     with a quarter of the arms B=2,615 69.1 / 77.3; K=32 B=16,384 211 / 213,
 //     127 / 129, 95 / 85, 80 / 74 (three); K=64 401 / 398, 219 / 223, 130 / 134,
@@ -407,7 +411,11 @@ constexpr int kSplitMinB = 8192;   // (twice that at d = 32)
 bool split_update(const agft_config &c, int64_t t, bool dump) {
     const size_t stream = (size_t)c.B * explore_bytes(c);
     if (dump && explore_bytes(c) <= 16384) return false;
-    const size_t least_mb = c.d != 8 ? 256 : dump || score_waves_at(c, t) == 1 ? 512 : 2048;
+    const bool arms_go = c.prune_rule != 0 || c.refine || c.exploit;
+    const size_t least_mb = c.d != 8 ? 256
+                          : dump ? 512
+                          : arms_go ? (score_waves_at(c, t) == 1 ? 512 : 2048)
+                          : explore_bytes(c) <= 24 * 1024 ? 512 : 1024;
     return c.B >= (c.d == 32 ? 2 * kSplitMinB : kSplitMinB) && stream >= least_mb << 20;
 }
 

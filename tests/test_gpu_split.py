@@ -33,7 +33,8 @@ def _split(B, K, d, opts, dump=False):
     each = play * 4 * (d + d * (d + 1) // 2)
     scored = play * 4 * d if "exploit" in opts else each   # (from the round of the first possible switch on)
     wide = scored > (96 if opts.get("prune_rule", 0) & 14 else 32) << 10
-    least = 256 if d != 8 else 2048 if wide and not dump else 512
+    arms_go = "prune_rule" in opts or "refine" in opts or "exploit" in opts
+    least = 256 if d != 8 else 512 if dump else (2048 if wide else 512) if arms_go else 1024 if each > 24 << 10 else 512
     return B >= (16384 if d == 32 else 8192) and B * each >= least << 20 and not (dump and each <= 16384)
 
 

@@ -59,8 +59,9 @@ def test_gpu_cases_take_two_launches(routes):
     (16, 128, dict(prune_rule=1), False, 8192), (16, 54, {}, False, 8192),      # instances bind: 256 MB are less
     (16, 53, {}, False, 8331), (16, 27, {}, False, 16353),                      # 256 MB bind
     (32, 96, dict(prune_rule=1), False, 16384), (32, 7, {}, False, 17120),
-    (8, 128, dict(prune_rule=1), False, 23832), (8, 186, {}, False, 16401),     # d = 8, one wavefront: 512 MB
-    (8, 187, {}, False, 65250), (8, 256, dict(prune_rule=1), False, 47663),     # four: 2 GB
+    (8, 128, dict(prune_rule=1), False, 23832), (8, 186, dict(prune_rule=1), False, 16401),   # d = 8, one wavefront: 512 MB
+    (8, 187, dict(prune_rule=1), False, 65250), (8, 256, dict(prune_rule=1), False, 47663),   # four: 2 GB
+    (8, 139, {}, False, 21946), (8, 140, {}, False, 43578), (8, 256, {}, False, 23832),   # no arm goes: 1 GB from 24 KB on
     (8, 256, RULES, False, 11916), (8, 600, RULES, False, 20337),               # the rules' own limit of widths
     (8, 256, dict(prune_rule=1), True, 11916),                                  # with the dump: 512 MB
     (16, 128, REFINE, False, 21025), (16, 128, REFINE, True, None),             # and none up to 16 KB
