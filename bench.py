@@ -489,6 +489,9 @@ def main():
     # workload with the switch take the exploring width)
     from paper_2508_01744_amd import launch_shape, workload_config
     res["detail"]["launch_shape"] = launch_shape(workload_config(wl))
+    res["detail"]["launch_shape_note"] = ("of a step in one launch; a large batch's update is a launch of its own, "
+                                          "and the step after it has one wavefront per workgroup up to 32 KB "
+                                          "streamed per instance (96 KB with rules 2-8), four beyond")
     if ceil_error is not None:
         res["roofline"]["ceiling"] = {"error": ceil_error}
     if ceil_busy is not None:

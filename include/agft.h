@@ -268,8 +268,8 @@ typedef struct agft_launch_shape {
                              take the exploring instance's width) */
     int32_t simd_waves;   /* wavefronts per SIMD the kernel's registers allow */
     int32_t tail_floats;  /* record layout, as agft_state_view.tail_floats */
-    int32_t early_update; /* 1: the rank-1 update runs while the stream's first pass
-                             is in flight; 0: after the stream */
+    int32_t early_update; /* 1: the rank-1 update runs ahead of the stream's second
+                             pass; 0: after the stream */
     int32_t cu_workgroups;  /* workgroups per compute unit agft_step's launch admits
                                (its LDS request caps them there, beyond 64 KB
                                streamed per instance); 0: no cap.

@@ -26,9 +26,11 @@
 //      instance reads only a contiguous copy of theta and scores m (Eq. 2);
 //   3. fold the previous decision's reward into its arm: Eq. 3-5 as a
 //      square-root rank-1 update of S (below) plus the matching theta
-//      update, in LDS while the stream's first pass is in flight; the
-//      updated arm is scored on x_t from LDS in the same operation order as
-//      the stream, and its record is written back at the end of the step;
+//      update, in LDS, once the arm's record and the stream's first pass,
+//      requested together, have landed; the updated arm is scored on x_t from
+//      LDS in the same operation order as the stream, and its record is
+//      written back at the end of the step (large batches: ahead of the step,
+//      in a kernel of its own);
 //   4. pruning when due (drop UCB_k < max_j LCB_j), argmax with ties to the
 //      lowest arm index; refinement of the action space when due; epilogue.
 //
@@ -327,13 +329,13 @@ int waves_at(const agft_config &c, int64_t t) {
     return waves_for(c);
 }
 
-// Whether the update of the previous decision's arm runs before the stream
-// (its first pass lands meanwhile and the chain gets shorter) rather than
-// after it: always, except at d = 32 where an instance streams more than
-// 16 KB, since there the longer update holds back the second pass (the
-// kernel still runs it before the stream at a step whose list of arms fits
-// in one pass).
-// Measured on MI355X (step kernel, before / after the stream): K=64 d=8
+// Whether the update of the previous decision's arm runs ahead of the stream,
+// when its record and the stream's first pass have landed, rather than after
+// it: always, except at d = 32 where an instance streams more than 16 KB, since
+// the second pass is requested only after it and the longer update holds that
+// back (the kernel still runs it first at a step whose list of arms fits in one
+// pass).
+// Measured on MI355X (step kernel, ahead of / after the stream): K=64 d=8
 // B=4,096 19.1 / 20.5 us; K=128 d=16 B=65,536 853 / 857 us, B=16,384 218.4 /
 // 220.8 us; K=256 d=32 B=1,024 92.4 / 91.7 us.
 bool early_update(const agft_config &c) { return c.d < 32 || explore_bytes(c) <= 16384; }
@@ -546,9 +548,9 @@ __device__ __forceinline__ float4 ld_nt(const float4 *p) {
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// The one record per instance that the update gathers and writes back takes
-// the same non-temporal hint only for d = 16.  Measured per step against
-// ordinary accesses: d = 16, -0.9% (65,536 x 128) and -0.4% (16,384 x 128);
+// The one record per instance that the step kernel's update gathers and writes
+// back takes the same non-temporal hint only for d = 16.  Measured per step
+// against ordinary accesses: d = 16, -0.9% (65,536 x 128) and -0.4% (16,384 x 128);
 // d = 8, +5% (4,096 x 64); d = 32, +3% (1,024 x 256).
 // The gather goes from memory to LDS without registers: 16 bytes per lane,
 // lane l's to dst[l] (dst the same in every lane).  It has landed once vmcnt
@@ -1244,9 +1246,9 @@ __device__ __forceinline__ void step_body(const StepArgs &p, const agft_env_deta
     };
 
     // ---- square-root rank-1 update of the previous decision's arm ----
-    // Run while the stream's first pass is in flight, or after the stream
-    // (early_update on the host decides which, and the kernel runs it early
-    // whenever the whole list fits in the first pass), in LDS; the updated
+    // Run when the record and the stream's first pass have landed, or after the
+    // stream (early_update on the host decides which, and the kernel runs it
+    // early whenever the whole list fits in the first pass), in LDS; the updated
     // record is written back as the kernel's last act (write_back below).
     auto update = [&]() {
         // (fused and separate products as written, here and in agft_update_kernel)
@@ -1728,7 +1730,11 @@ void agft_score_kernel(StepArgs p) {
 // kernel's own update for workgroups of ORDER wavefronts, so the results are
 // the same bits.  Bound by the round trips to the instance's words and then to
 // its record, and by HBM: 65,536 instances at d = 16 take 24 us (80 MB of
-// records read and written), 16,384 take 8.6 us.
+// records read and written), 16,384 take 8.6 us.  The records go back with the
+// non-temporal hint at every d: with nothing else in the kernel it makes no
+// difference at d = 8 and 32 (us per step with and without: 65,536 x 128 x 8 284.2
+// / 284.8, 16,384 x 64 x 32 399.5 / 399.9, with eight arms left 52.2 / 51.5 and
+// 86.4 / 86.4).
 constexpr int kUpdateThreads = 256;
 template <int D, int TF, int ORDER>
 __global__ __launch_bounds__(kUpdateThreads) void agft_update_kernel(StepArgs p) {
